@@ -468,7 +468,9 @@ void igemm_set_frame(IgemmArgs& a, const int bands[4]) {
 bool igemm_plan(IgemmArgs& a, int dtype) {
     a.kind = 0;
     // a merged-phase backward-data request runs on the register-weight kernel or not at all
-    if (a.bp) return dtype == 1 && igemm_wreg_plan(a);
+    // (C <= 8) or on the blocked kernel
+    if (a.bp == 1) return dtype == 1 && igemm_wreg_plan(a);
+    if (a.bp == 2) return igemm_tile_plan(a, dtype);
     // a frame runs on the frame kernel, else on the chunked kernel (the strip
     // kernels cover whole tiles)
     if (a.frame && igemm_frame_plan(a, dtype)) return true;
@@ -476,6 +478,7 @@ bool igemm_plan(IgemmArgs& a, int dtype) {
         if (dtype == 1 && igemm_roll_plan(a)) return true;
         if (dtype == 1 && igemm_wreg_plan(a)) return true;
         if (dtype == 0 && igemm_f32w_plan(a)) return true;
+        if (igemm_tile_plan(a, dtype)) return true;
     }
     a.OB = a.Cout <= 32 ? 32 : 64;
     // channel-chunk candidates, widest first: the channel count itself (rounded
@@ -512,6 +515,7 @@ hipError_t launch_igemm(const IgemmArgs& a, int dtype, hipStream_t s) {
     if (a.kind == 2) return launch_igemm_f32w(a, s);
     if (a.kind == 3) return launch_igemm_roll(a, s);
     if (a.kind == 4) return launch_igemm_frame(a, dtype, s);
+    if (a.kind == 5) return launch_igemm_tile(a, dtype, s);
     const int nvb = (a.Vo + kBW - 1) / kBW, nub = (a.Uo + kBH - 1) / kBH;
     dim3 grid(a.frame ? a.fblk[a.fseg] : nvb * nub, (a.Cout + a.OB - 1) / a.OB, a.ntiles * a.Nn);
     if (grid.x == 0) return hipSuccess;   // an empty frame

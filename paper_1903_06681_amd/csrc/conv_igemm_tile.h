@@ -1,0 +1,567 @@
+// Forward and backward-data convolution of layers of any channel count,
+// filter, image size and stride on gfx950 matrix cores: a blocked implicit
+// GEMM with both operands staged in LDS (Eqs. (1) and (3) of Sec. II-A on the
+// tile of Sec. III-A).
+//
+//   D[o][pixel] = sum over (tap, input channel) of A[o][tap, ci] * B[tap, ci][pixel]
+//
+// Work split.  A workgroup of four waves computes OB output channels of a
+// block of BU x BV output pixels of one image, flattened: pixel p of the block
+// is MFMA column p, so narrow images (7 to 56 columns) fill the columns that a
+// fixed 64-wide strip leaves empty.  The input channels are walked in chunks
+// of 8 CCG; the next chunk's global loads are issued before the MFMA loop of
+// the present one and written to LDS after it, and two workgroups share a
+// CU, so that one computes while the other stages.
+//
+// LDS layout.  Both operands lie as 16-byte records of eight channels (what a
+// lane of v_mfma_f32_32x32x16_bf16 reads): weights [plane][tap][group][o],
+// the input patch [row][column][plane, group] with an odd number of records a
+// pixel (conflict-free reads of neighbouring pixels).  The tap's shift is an
+// offset common to all lanes.  At input stride 2 even and odd columns lie
+// apart, so that the pixels of a tap are neighbours again.  NCHW rows are
+// transposed on the way in: 16-byte loads of 8 channels, one byte permute per
+// two values.
+//
+// fp32 layers run on the same matrix instruction.  Each value is split into
+// three bf16 parts that add up to it exactly (three roundings to nearest, 24
+// bits), and the product is formed from the six part products of weight above
+// 2^-24 (parts 0*0, 0*1, 1*0, 1*1, 0*2, 2*0); what is left out is about 2^-26
+// of a product and of random sign.  Six bf16 MFMAs take 16 channels in 192
+// cycles; v_mfma_f32_32x32x2_f32 takes 512.  Values the parts cannot hold
+// (infinities, NaN, magnitudes near the ends of the range) are noticed while
+// staging, and the workgroup then computes its block in plain fp32.
+//
+// Bound: the matrix cores at many channels; what holds it is staging (waits
+// for loads and barriers, 2 waves per SIMD).  Measured against the chunked
+// kernel it replaces for these layers (us a pass): 128 -> 128 channels 3x3 on
+// 32 images of 28x28, bf16: 131 -> 21; 256 -> 256 3x3 stride 2 on 28x28:
+// forward 286 -> 35, backward-data 274 -> 33; fp32 128 -> 128 3x3 on a 64x64
+// tile: 208 -> 43 and 210 -> 40; fp32 32 -> 32 stride 2 on a 512x512 tile,
+// backward-data: 89 -> 20.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "bf16util.h"
+#include "kernels.h"
+
+namespace dc {
+
+static constexpr int kTileThreads = 256;
+static constexpr int kTileWord3 = 0x00020000;   // buffer resource word 3 (gfx9 family: raw access)
+// Byte offset past every buffer here, whatever channel offset is added (the
+// plan keeps those below 2^31): such a load returns 0, such a store is dropped.
+static constexpr uint32_t kTileOut = 0x80000000u;
+// magnitudes above this could overflow in a part product while the fp32 product does not
+static constexpr float kTileBig = 4.611686e18f;   // 2^62
+
+// weight staging: per-element gathers (any layout); forward, a thread's 8
+// channels x T taps as T 16-byte loads; backward-data, 8 x 8 blocks
+enum { kWGather = 0, kWRows = 1, kWBlocks = 2 };
+
+__host__ __device__ constexpr int tile_psu(int NS, int CCG) { return (NS * CCG) | 1; }
+// weight records per channel group and per tap: neighbouring groups and taps
+// start in other banks, as a wave's writes go to several of them at once
+__host__ __device__ constexpr int tile_grec(int OB) { return OB + 1; }
+__host__ __device__ constexpr int tile_trec(int CCG, int OB) { return (CCG * tile_grec(OB)) | 1; }
+
+// e / d for e, d < 2^16 by the host's m = 2^32 / d + 1 (0 for d = 1)
+__device__ __forceinline__ int tile_div(int e, uint32_t m) { return m ? int(__umulhi(uint32_t(e), m)) : e; }
+
+// 8 fp32 values -> three records of bf16 parts; `bad` collects what the parts
+// do not hold, `mx` the largest magnitude
+__device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], uint32_t& bad, float& mx) {
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = f[2 * i], b = f[2 * i + 1];
+        mx = fmaxf(mx, fmaxf(fabsf(a), fabsf(b)));
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf2));
+            a -= __builtin_bit_cast(float, u << 16);
+            b -= __builtin_bit_cast(float, u & 0xffff0000u);
+            w[s][i] = u;
+        }
+        bad |= __builtin_bit_cast(uint32_t, a) | __builtin_bit_cast(uint32_t, b);
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s) p[s] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};
+}
+
+// element e of an array of 16-bit values held in 32-bit words
+template <int N>
+__device__ __forceinline__ uint32_t pair16(const uint32_t (&d)[N], int e0, int e1) {   // (e0 low, e1 high)
+    const uint32_t lo = d[e0 >> 1], hi = d[e1 >> 1];
+    const uint32_t sel = ((e0 & 1) ? 0x0302u : 0x0100u) | ((e1 & 1) ? 0x07060000u : 0x05040000u);
+    return __builtin_amdgcn_perm(hi, lo, sel);
+}
+
+// One output element in plain fp32, straight from the tensors: the path of
+// blocks whose values the bf16 parts cannot hold.
+__device__ inline float tile_direct(const IgemmArgs& a, const float* in, const float* w, int o, int u, int v,
+                                    int ph) {
+    const int py = ph >> 1, px = ph & 1;
+    const int ntr = a.bp ? a.bptr[py] : a.Tr, nts = a.bp ? a.bpts[px] : a.Ts;
+    const int dr = a.bp ? a.bpdr[py] : 0, dc_ = a.bp ? a.bpdc[px] : 0;
+    const int r0 = a.bp ? a.bpr0[py] : a.wr0, rs = a.bp ? -2 : a.wrstep;
+    const int s0 = a.bp ? a.bps0[px] : a.ws0, ss = a.bp ? -2 : a.wsstep;
+    const int64_t plane = int64_t(a.in_rows) * a.in_pitch;
+    float sum = 0.f;
+    for (int ci = 0; ci < a.Cin; ++ci)
+        for (int tr = 0; tr < ntr; ++tr)
+            for (int ts = 0; ts < nts; ++ts) {
+                const int gr = u * a.istr + a.base_r + dr + tr, gc = v * a.istr + a.base_c + dc_ + ts;
+                if (gr < 0 || gr >= a.in_rows || gc < 0 || gc >= a.in_cols) continue;
+                sum = fmaf(w[o * a.w_os + ci * a.w_cs + (r0 + rs * tr) * a.S + s0 + ss * ts],
+                           in[ci * plane + int64_t(gr) * a.in_pitch + gc], sum);
+            }
+    return sum;
+}
+
+hipError_t launch_tile_bf16(const IgemmArgs& a, hipStream_t s);
+hipError_t launch_tile_bf16_bp(const IgemmArgs& a, hipStream_t s);
+hipError_t launch_tile_f32(const IgemmArgs& a, hipStream_t s);
+
+// NS: parts per value (1: bf16 tensors, 3: fp32); CCG: 8-channel groups per
+// chunk; a wave computes NOBW x NPBW MFMA tiles, WO x WP waves; WM, TT: weight
+// staging and its taps (kWRows); WPT, UPT: weight and patch units per thread
+// held in registers; BP: the four output phases of a stride-2 backward-data
+// together (each tap belongs to one phase; the input patch is shared and the
+// two column phases leave as 8-byte stores).
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP>
+__global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    static_assert(WO * WP == 4, "four waves");
+    static_assert(NS == 1 || WM == kWGather, "fp32 weights are gathered");
+    constexpr int OB = 32 * NOBW * WO, CC = 8 * CCG, NPH = BP ? 4 : 1;
+    constexpr int ES = NS == 1 ? 2 : 4;
+    constexpr int GW = 16 / ES;             // pixels of a staged 16-byte vector
+    constexpr int PSU = tile_psu(NS, CCG);  // records per pixel
+    constexpr int GREC = tile_grec(OB), TREC = tile_trec(CCG, OB);
+
+    // pixel blocks round-robin over the XCDs, the output-channel blocks of one
+    // pixel block in turn on the same XCD (its patch comes from one L2)
+    const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+    const int ob = idx % a.tnob, pbk = (idx / a.tnob) * 8 + xcd;
+    if (pbk >= a.tnpb) return;
+    const int per = a.tnub * a.nvb;
+    const int z = pbk / per, inb = pbk - z * per;
+    const int ub = inb / a.nvb, vb = inb - ub * a.nvb;
+    const int tile = z / a.Nn, n = z - tile * a.Nn;
+    const int u0 = ub * a.tbu, v0 = vb * a.tbv;
+    const int bu = min(a.tbu, a.Uo - u0), bv = a.tbv;   // columns past Vo: computed, not stored
+    const int o0 = ob * OB;
+    const int T = a.R * a.S;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int wo = wave / WP, wp = wave % WP;
+
+    const int plane = a.in_rows * a.in_pitch;
+    const char* in = static_cast<const char*>(a.in) + (tile * a.in_tile + int64_t(n) * a.Cin * plane) * ES;
+    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(in), 0, a.Cin * plane * ES, kTileWord3);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void*>(a.w), 0, a.wK * a.wC * T * ES, kTileWord3);
+
+    uint4* wl = reinterpret_cast<uint4*>(smem);   // [NS][T][CCG][OB], a record of pad per tap
+    uint4* pl = wl + NS * T * TREC;               // [PR][ROW][PSU]
+    const int WPL = T * TREC;
+    const int PG = a.tpg, PR = (bu - 1) * a.istr + a.Tr;   // 8-pixel groups per row, rows
+    const int ROW = PG * GW;
+    const int cin0 = v0 * a.istr + a.base_c, ca = cin0 & ~(GW - 1), sh = cin0 - ca;
+    const int row0 = u0 * a.istr + a.base_r;
+    const bool de = a.istr == 2;   // even and odd columns apart
+
+    // ---- staging units of this thread
+    uint32_t poff[UPT];            // patch: byte offset for channel group 0 of a chunk
+    int pslot[UPT], plim[UPT];     // LDS record of pixel 0 (-1: none), columns left in the padded row
+    const uint32_t pstep = uint32_t(plane) * ES;   // bytes per channel
+    auto patch_unit = [&](int e, uint32_t& off, int& slot, int& lim) __attribute__((always_inline)) {
+        const int cg = e % CCG, rest = e / CCG;
+        const int pr = tile_div(rest, a.tmpg), g = rest - pr * PG;
+        const int gr = row0 + pr, gc = ca + g * GW;
+        const bool in_lds = pr < PR, ok = in_lds & (gr < a.in_rows) & (gc < a.in_pitch);
+        off = ok ? uint32_t(gr * a.in_pitch + gc) * ES + cg * 8 * pstep : kTileOut;
+        slot = in_lds ? (pr * ROW + (de ? g * (GW / 2) : g * GW)) * PSU + cg : -1;
+        lim = a.in_cols - gc;
+    };
+    const int npu = PR * PG * CCG;
+#pragma unroll
+    for (int q = 0; q < UPT; ++q) patch_unit(tid + q * kTileThreads, poff[q], pslot[q], plim[q]);
+
+    // weight units: kWGather (tap, group, o) with taps fastest; kWRows (o,
+    // group); kWBlocks (group, 8 consecutive (o, tap))
+    const int NFG = OB * T / 8;
+    const int nwu = WM == kWGather ? T * CCG * OB : WM == kWRows ? OB * CCG : NFG * CCG;
+    const uint32_t wstep = uint32_t(a.w_cs) * ES;   // bytes per input channel
+    uint32_t woff[WPT];
+    int wslot[WPT], wcg[WPT];
+    auto w_unit = [&](int e, uint32_t& off, int& slot, int& cg) __attribute__((always_inline)) {
+        const bool in_lds = e < nwu;
+        if constexpr (WM == kWGather) {
+            const int rest = tile_div(e, a.tmt), t = e - rest * T;
+            const int o = a.wmode ? rest % OB : rest / CCG;
+            cg = a.wmode ? rest / OB : rest % CCG;
+            off = in_lds & (o0 + o < a.Cout) ? uint32_t(int((o0 + o) * a.w_os) + t) * ES + cg * 8 * wstep : kTileOut;
+            slot = in_lds ? t * TREC + cg * GREC + o : -1;
+        } else if constexpr (WM == kWRows) {
+            cg = e % CCG;
+            const int o = e / CCG;
+            off = in_lds & (o0 + o < a.Cout) ? uint32_t((o0 + o) * int(a.w_os)) * ES + cg * 8 * wstep : kTileOut;
+            slot = in_lds ? cg * GREC + o : -1;
+        } else {
+            cg = tile_div(e, a.tmnf);
+            const int f = (e - cg * NFG) * 8;
+            off = in_lds & (o0 * T + f < a.Cout * T) ? uint32_t(o0 * T + f) * ES + cg * 8 * wstep : kTileOut;
+            slot = in_lds ? f : -1;
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < WPT; ++q) w_unit(tid + q * kTileThreads, woff[q], wslot[q], wcg[q]);
+
+    constexpr int WV = WM == kWRows ? TT : 8;   // vectors (or elements) of a weight unit
+    typedef uint32_t u32;
+    // channels past Cin: past the sample's end, zero
+    auto load_patch = [&](uint4 (&v)[8], uint32_t off, int c0) __attribute__((always_inline)) {
+        off += c0 * pstep;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            v[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rin, off + j * pstep, 0, 0));
+    };
+    uint32_t bad = 0;
+    float mx = 0.f;
+    auto store_patch = [&](const uint4 (&v)[8], int slot, int lim) __attribute__((always_inline)) {
+        if (slot < 0) return;
+        const int step = PSU, odd = de ? (ROW / 2) * PSU : 0;
+        if constexpr (NS == 1) {
+            u32 d[8][4];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { d[j][0] = v[j].x; d[j][1] = v[j].y; d[j][2] = v[j].z; d[j][3] = v[j].w; }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const u32 sel = (i & 1) ? 0x07060302u : 0x05040100u;
+                uint4 r;
+                r.x = __builtin_amdgcn_perm(d[1][i / 2], d[0][i / 2], sel);
+                r.y = __builtin_amdgcn_perm(d[3][i / 2], d[2][i / 2], sel);
+                r.z = __builtin_amdgcn_perm(d[5][i / 2], d[4][i / 2], sel);
+                r.w = __builtin_amdgcn_perm(d[7][i / 2], d[6][i / 2], sel);
+                pl[slot + (de ? (i / 2) * step + (i & 1) * odd : i * step)] = r;
+            }
+        } else {
+            float f[8][4];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                f[j][0] = __builtin_bit_cast(float, v[j].x); f[j][1] = __builtin_bit_cast(float, v[j].y);
+                f[j][2] = __builtin_bit_cast(float, v[j].z); f[j][3] = __builtin_bit_cast(float, v[j].w);
+            }
+            // columns of the pitch hold anything and feed no stored pixel
+            if (lim < GW) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i >= lim)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) f[j][i] = 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float g[8] = {f[0][i], f[1][i], f[2][i], f[3][i], f[4][i], f[5][i], f[6][i], f[7][i]};
+                uint4 p[3];
+                split8(g, p, bad, mx);
+                const int at = slot + (de ? (i / 2) * step + (i & 1) * odd : i * step);
+#pragma unroll
+                for (int s = 0; s < 3; ++s) pl[at + s * CCG] = p[s];
+            }
+        }
+    };
+    // channels past Cin lie in the next row of a forward weight tensor: masked
+    auto load_w = [&](uint4 (&v)[WV], uint32_t off, int cg, int c0) __attribute__((always_inline)) {
+        const int left = a.Cin - c0 - cg * 8;
+        off += c0 * wstep;
+        if constexpr (WM == kWRows) {
+            off |= left > 0 ? 0u : kTileOut;
+#pragma unroll
+            for (int i = 0; i < TT; ++i)
+                v[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, off + 16 * i, 0, 0));
+        } else if constexpr (WM == kWBlocks) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     rw, (off + j * wstep) | (j < left ? 0u : kTileOut), 0, 0));
+        }
+    };
+    auto load_g = [&](u32 (&v)[8], uint32_t off, int cg, int c0) __attribute__((always_inline)) {
+        const int left = a.Cin - c0 - cg * 8;
+        off += c0 * wstep;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t b = (off + j * wstep) | (j < left ? 0u : kTileOut);
+            if constexpr (NS == 1) v[j] = __builtin_amdgcn_raw_buffer_load_b16(rw, b, 0, 0);
+            else v[j] = __builtin_amdgcn_raw_buffer_load_b32(rw, b, 0, 0);
+        }
+    };
+    auto store_g = [&](const u32 (&v)[8], int slot) __attribute__((always_inline)) {
+        if (slot < 0) return;
+        if constexpr (NS == 1) {
+            uint4 r;
+            r.x = v[0] | (v[1] << 16); r.y = v[2] | (v[3] << 16);
+            r.z = v[4] | (v[5] << 16); r.w = v[6] | (v[7] << 16);
+            wl[slot] = r;
+        } else {
+            float f[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = __builtin_bit_cast(float, v[j]);
+            uint4 p[3];
+            split8(f, p, bad, mx);
+#pragma unroll
+            for (int s = 0; s < 3; ++s) wl[s * WPL + slot] = p[s];
+        }
+    };
+    auto store_w = [&](const uint4 (&v)[WV], int slot, int cg) __attribute__((always_inline)) {
+        if (slot < 0) return;
+        if constexpr (WM == kWRows) {
+            u32 d[4 * TT];
+#pragma unroll
+            for (int i = 0; i < TT; ++i) { d[4 * i] = v[i].x; d[4 * i + 1] = v[i].y; d[4 * i + 2] = v[i].z; d[4 * i + 3] = v[i].w; }
+#pragma unroll
+            for (int t = 0; t < TT; ++t)
+                wl[t * TREC + slot] = uint4{pair16(d, t, TT + t), pair16(d, 2 * TT + t, 3 * TT + t),
+                                            pair16(d, 4 * TT + t, 5 * TT + t), pair16(d, 6 * TT + t, 7 * TT + t)};
+        } else if constexpr (WM == kWBlocks) {
+            u32 d[8][4];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { d[j][0] = v[j].x; d[j][1] = v[j].y; d[j][2] = v[j].z; d[j][3] = v[j].w; }
+            int o = tile_div(slot, a.tmt), t = slot - o * T;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const u32 sel = (i & 1) ? 0x07060302u : 0x05040100u;
+                uint4 r;
+                r.x = __builtin_amdgcn_perm(d[1][i / 2], d[0][i / 2], sel);
+                r.y = __builtin_amdgcn_perm(d[3][i / 2], d[2][i / 2], sel);
+                r.z = __builtin_amdgcn_perm(d[5][i / 2], d[4][i / 2], sel);
+                r.w = __builtin_amdgcn_perm(d[7][i / 2], d[6][i / 2], sel);
+                wl[t * TREC + cg * GREC + o] = r;
+                const bool wrap = ++t == T;
+                t = wrap ? 0 : t;
+                o += wrap ? 1 : 0;
+            }
+        }
+    };
+
+    uint4 xs[UPT][8];
+    uint4 ws[WM == kWGather ? 1 : WPT][WV];
+    u32 gs[WM == kWGather ? WPT : 1][8];
+    auto load_chunk = [&](int c0) __attribute__((always_inline)) {
+        if constexpr (WM == kWGather) {
+#pragma unroll
+            for (int q = 0; q < WPT; ++q) load_g(gs[q], woff[q], wcg[q], c0);
+        } else {
+#pragma unroll
+            for (int q = 0; q < WPT; ++q) load_w(ws[q], woff[q], wcg[q], c0);
+        }
+#pragma unroll
+        for (int q = 0; q < UPT; ++q) load_patch(xs[q], poff[q], c0);
+    };
+    auto store_chunk = [&](int c0) __attribute__((always_inline)) {
+        if constexpr (WM == kWGather) {
+#pragma unroll
+            for (int q = 0; q < WPT; ++q) store_g(gs[q], wslot[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < UPT; ++q) store_patch(xs[q], pslot[q], plim[q]);
+        // units beyond the registers' share
+        for (int e = tid + WPT * kTileThreads; e < nwu; e += kTileThreads) {
+            uint32_t off;
+            int slot, cg;
+            w_unit(e, off, slot, cg);
+            if constexpr (WM == kWGather) {
+                u32 v[8];
+                load_g(v, off, cg, c0);
+                store_g(v, slot);
+            } else {
+                uint4 v[WV];
+                load_w(v, off, cg, c0);
+                store_w(v, slot, cg);
+            }
+        }
+        for (int e = tid + UPT * kTileThreads; e < npu; e += kTileThreads) {
+            uint32_t off;
+            int slot, lim;
+            patch_unit(e, off, slot, lim);
+            uint4 v[8];
+            load_patch(v, off, c0);
+            store_patch(v, slot, lim);
+        }
+    };
+
+    floatx16 acc[NPH][NOBW][NPBW];
+#pragma unroll
+    for (int ph = 0; ph < NPH; ++ph)
+#pragma unroll
+        for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+            for (int j = 0; j < NPBW; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[ph][i][j][e] = 0.f;
+
+    // this lane's pixels (past the block's last: a repeat of it, never stored)
+    const int np = bu * bv;
+    int pix[NPBW];
+#pragma unroll
+    for (int j = 0; j < NPBW; ++j) {
+        const int p = min((wp * NPBW + j) * 32 + l32, np - 1);
+        const int ul = tile_div(p, a.tmbv), vl = p - ul * bv;
+        pix[j] = (ul * a.istr * ROW + (de ? vl : vl * a.istr)) * PSU;
+    }
+    const int abase = wo * 32 * NOBW + l32;
+    auto tap_b = [&](int tr, int ts) __attribute__((always_inline)) {   // record offset of tap (tr, ts)
+        const int c = sh + ts;
+        return (tr * ROW + (de ? (c >> 1) + (c & 1) * (ROW / 2) : c)) * PSU;
+    };
+    // one k-step: records ar of the weights, br of the patch (per lane half)
+    auto kstep = [&](int ar, int br, bool zero, floatx16 (&c)[NOBW][NPBW]) __attribute__((always_inline)) {
+        bf16x8 A[NS][NOBW], B[NS][NPBW];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+#pragma unroll
+            for (int i = 0; i < NOBW; ++i) {
+                uint4 r = wl[s * WPL + ar + abase + i * 32];
+                if (zero) r = uint4{0, 0, 0, 0};
+                A[s][i] = __builtin_bit_cast(bf16x8, r);
+            }
+#pragma unroll
+            for (int j = 0; j < NPBW; ++j) {
+                uint4 r = pl[br + pix[j] + s * CCG];
+                if (zero) r = uint4{0, 0, 0, 0};
+                B[s][j] = __builtin_bit_cast(bf16x8, r);
+            }
+        }
+        constexpr int NP = NS == 1 ? 1 : 6;
+        constexpr int pa[6] = {0, 2, 1, 1, 0, 0}, pb[6] = {2, 0, 1, 0, 1, 0};   // small products first
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+#pragma unroll
+            for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                for (int j = 0; j < NPBW; ++j)
+                    c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[NS == 1 ? 0 : pa[k]][i],
+                                                                      B[NS == 1 ? 0 : pb[k]][j], c[i][j], 0, 0, 0);
+    };
+
+    const int cin = a.Tr > 0 ? a.Cin : 0;   // an output phase without taps is zero
+    if (cin > 0) load_chunk(0);
+    for (int c0 = 0; c0 < cin; c0 += CC) {
+        if (c0 > 0) __syncthreads();
+        store_chunk(c0);
+        __syncthreads();
+        if (c0 + CC < cin) load_chunk(c0 + CC);
+        const int ng = min(CCG, (a.Cin - c0 + 7) / 8);   // channel groups of this chunk
+#pragma unroll
+        for (int ph = 0; ph < NPH; ++ph) {
+            const int py = ph >> 1, px = ph & 1;
+            const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
+            const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
+            const int r0 = BP ? a.bpr0[py] : a.wr0, rs = BP ? -2 : a.wrstep;
+            const int s0 = BP ? a.bps0[px] : a.ws0, ss = BP ? -2 : a.wsstep;
+            for (int tr = 0; tr < ntr; ++tr)
+                for (int ts = 0; ts < nts; ++ts) {
+                    const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
+#pragma unroll
+                    for (int g = 0; g + 1 < CCG; g += 2)
+                        if (g + 1 < ng) kstep(ao + (g + hi) * GREC, bo + g + hi, false, acc[ph]);
+                }
+            if (ng & 1) {
+                // a last lone group: two taps per k-step, one per half of the lanes
+                const int g = ng - 1, nt = ntr * nts;
+                int tr1 = 0, ts1 = 0;
+                for (int i = 0; i < nt; i += 2) {
+                    int tr2 = tr1, ts2 = ts1;
+                    if (i + 1 < nt && ++ts2 == nts) { ts2 = 0; ++tr2; }
+                    const int tr = hi ? tr2 : tr1, ts = hi ? ts2 : ts1;
+                    const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
+                    kstep(ao + g * GREC, bo + g, (i + 1 >= nt) & hi, acc[ph]);
+                    tr1 = tr2; ts1 = ts2;
+                    if (++ts1 == nts) { ts1 = 0; ++tr1; }
+                }
+            }
+        }
+    }
+
+    // D of a 32x32 tile: value e of lane l is row 8*(e/4) + 4*(l/32) + e%4
+    // (output channel), column l%32 (pixel)
+    const int oplane = a.out_rows * a.out_cols;
+    float* out = a.out + tile * a.out_tile + int64_t(n) * a.Cout * oplane;
+    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.Cout * oplane * 4, kTileWord3);
+    if constexpr (NS == 3) {
+        if (__syncthreads_or(int(bad != 0 || mx > kTileBig))) {
+            const float* inf = reinterpret_cast<const float*>(in);
+            const float* wf = static_cast<const float*>(a.w);
+            for (int e = tid; e < OB * np * NPH; e += kTileThreads) {
+                const int p = e % np, rest = e / np;
+                const int ph = rest % NPH, o = o0 + rest / NPH;
+                const int ul = p / bv, u = u0 + ul, v = v0 + p - ul * bv;
+                if (v >= a.Vo) continue;
+                const int orow = u * a.ostr + (BP ? ph >> 1 : a.oph_r), ocol = v * a.ostr + (BP ? ph & 1 : a.oph_c);
+                if (o >= a.Cout || orow >= a.out_rows || ocol >= a.out_cols) continue;
+                out[int64_t(o) * oplane + int64_t(orow) * a.out_cols + ocol] = tile_direct(a, inf, wf, o, u, v, ph);
+            }
+            return;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NPBW; ++j) {
+        const int p = (wp * NPBW + j) * 32 + l32;
+        const int ul = tile_div(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
+        const bool live = (p < np) & (v < a.Vo);
+#pragma unroll
+        for (int i = 0; i < NOBW; ++i) {
+            const int ob0 = o0 + (wo * NOBW + i) * 32 + 4 * hi;
+            if constexpr (BP) {
+#pragma unroll
+                for (int py = 0; py < 2; ++py) {
+                    const int orow = 2 * u + py, ocol = 2 * v;
+                    const bool ok = live && orow < a.out_rows, both = ocol + 1 < a.out_cols;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int o = ob0 + 8 * (e / 4) + e % 4;
+                        const uint32_t off = (o * oplane + orow * a.out_cols + ocol) * 4;
+                        const float f0 = acc[2 * py][i][j][e], f1 = acc[2 * py + 1][i][j][e];
+                        typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+                        const u32x2 w2 = {__builtin_bit_cast(u32, f0), __builtin_bit_cast(u32, f1)};
+                        __builtin_amdgcn_raw_buffer_store_b64(w2, rout, ok & both & (o < a.Cout) ? off : kTileOut, 0, 0);
+                        if (!both & ok & (o < a.Cout)) __builtin_amdgcn_raw_buffer_store_b32(w2[0], rout, off, 0, 0);
+                    }
+                }
+            } else {
+                const int orow = u * a.ostr + a.oph_r, ocol = v * a.ostr + a.oph_c;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int o = ob0 + 8 * (e / 4) + e % 4;
+                    const uint32_t off = (o * oplane + orow * a.out_cols + ocol) * 4;
+                    const float f = acc[0][i][j][e];
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, f), rout,
+                                                          live & (o < a.Cout) ? off : kTileOut, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP>
+static hipError_t launch_tile(const IgemmArgs& a, hipStream_t s) {
+    auto k = igemm_tile_kernel<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP>;
+    if (a.lds_bytes > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k, dim3((a.tnpb + 7) / 8 * 8 * a.tnob), dim3(kTileThreads), a.lds_bytes, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace dc

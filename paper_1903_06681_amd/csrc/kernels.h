@@ -76,16 +76,24 @@ struct IgemmArgs {
     int OB;                      // output channels per workgroup (32 or 64)
     int lds_bytes;
     int kind;                    // 0: chunked kernel; 1, 2: register-weight strip kernel (bf16, fp32);
-                                 // 3: register-weight rolling-row kernel (bf16); 4: frame kernel (bf16, fp32)
+                                 // 3: register-weight rolling-row kernel (bf16); 4: frame kernel (bf16, fp32);
+                                 // 5: blocked kernel (bf16, fp32)
     int phase;                   // register-weight bf16 forward over the stride-2 phase images
-    // merged-phase backward-data (stride 2, C <= 8): all four output phases
-    // as one stride-1 correlation over dy; rows o' = 4 c + 2 py + px of the
-    // weight image, window origin (base_r, base_c).  bp: requested by the
+    // merged-phase backward-data (stride 2): all four output phases over one
+    // window of dy, origin (base_r, base_c).  bp 1 (C <= 8): one stride-1
+    // correlation, rows o' = 4 c + 2 py + px of the weight image; bp 2: the
+    // blocked kernel, each tap for its own phase.  bp: requested by the
     // caller; bpC: C; bpvoff: pixels the strips start early (16-byte aligned
     // staging); per row phase py: window-row offset bpdr, taps bptr, first
     // filter row bpr0 (then -2 per window row); per column phase likewise
     int bp, bpC, bpvoff;
     int bpdr[2], bptr[2], bpr0[2], bpdc[2], bpts[2], bps0[2];
+    // blocked kernel: instantiation (tile configuration, channel groups per
+    // chunk, weight staging), output-channel blocks, pixel blocks of tbu x tbv
+    // (tnub block rows x nvb block columns per image, tnpb in all), 16-byte
+    // vectors per patch row
+    int tcfg, tccg, twm, tnob, tnpb, tbu, tbv, tnub, tpg;
+    uint32_t tmt, tmpg, tmbv, tmnf;   // 2^32 / d + 1 of the kernel's divisors (0 for 1)
     int nvb, nseg, rows_per_seg; // strip kernels: 64- (128-, rolling) column strips, row segments
     // frame mode (chunked and frame kernels): the launch covers only the
     // output rectangles [fu0, fu0 + fnu) x [fv0, fv0 + fnv) of fseg segments,
@@ -114,6 +122,8 @@ bool igemm_roll_plan(IgemmArgs& a);
 hipError_t launch_igemm_roll(const IgemmArgs& a, hipStream_t s);
 bool igemm_f32w_plan(IgemmArgs& a);
 hipError_t launch_igemm_f32w(const IgemmArgs& a, hipStream_t s);
+bool igemm_tile_plan(IgemmArgs& a, int dtype);
+hipError_t launch_igemm_tile(const IgemmArgs& a, int dtype, hipStream_t s);
 bool igemm_frame_plan(IgemmArgs& a, int dtype);
 hipError_t launch_igemm_frame(const IgemmArgs& a, int dtype, hipStream_t s);
 

@@ -1,0 +1,114 @@
+"""The blocked kernels (any channel count, image size and stride) against the
+undecomposed oracle, at the sizes where their blocks, chunks and staging units
+end: lone channel groups, partial chunks, partial output blocks, images of a
+few pixels, one and several block columns, odd sizes at stride 2.
+
+Tolerance: an output adds n <= 3200 products in 32 bits; with random signs the
+rounding errors add up to about sqrt(n) * 2^-25 of the largest sums, 2e-6,
+and fp32 parts leave out less than 2^-24 of a product.  1e-5 of the largest
+output is five times that.
+"""
+import numpy as np
+import pytest
+import torch
+
+import harness as H
+import oracle as orc
+import paper_1903_06681_amd as dc
+import workloads as wl
+from workloads import Layer
+
+pytestmark = pytest.mark.gpu
+ALL, X, DY = dc.DC_ALL_TILES, dc.DC_X, dc.DC_DY
+
+
+def _layer(dtype, N, C, K, Hh, W, R, stride=1, P=1, Q=1, halo=None, seed=900):
+    return Layer("blocked", N, C, K, Hh, W, R, R, stride, R // 2, P, Q, R // 2 if halo is None else halo,
+                 dtype, "uniform", seed + C + K)
+
+
+LAYERS = [
+    # 3x3: whole chunks, a lone last group, fewer than 8 channels, filters past a block of 64
+    _layer("bf16", 2, 128, 128, 14, 14, 3), _layer("bf16", 1, 40, 72, 31, 25, 3), _layer("bf16", 2, 5, 33, 9, 130, 3),
+    _layer("bf16", 1, 72, 40, 16, 24, 3, P=2, Q=2), _layer("bf16", 3, 96, 160, 7, 7, 3),
+    _layer("f32", 2, 40, 72, 14, 14, 3), _layer("f32", 1, 36, 33, 9, 131, 3), _layer("f32", 1, 64, 40, 16, 24, 3, P=2, Q=2),
+    # a margin wider than the padding: unaligned first columns
+    _layer("bf16", 1, 24, 24, 26, 39, 3, P=2, Q=3, halo=2), _layer("f32", 1, 24, 24, 26, 39, 3, P=2, Q=3, halo=3),
+    # stride 2: odd sizes (phases of unequal extent), tiles, 1x1 (phases without taps), 5x5
+    _layer("bf16", 2, 48, 40, 25, 23, 3, 2), _layer("bf16", 1, 64, 96, 32, 32, 3, 2, 2, 2), _layer("bf16", 2, 40, 24, 15, 18, 1, 2),
+    _layer("bf16", 1, 24, 20, 36, 44, 5, 2, 2, 2), _layer("f32", 2, 36, 20, 25, 23, 3, 2), _layer("f32", 1, 40, 24, 15, 18, 1, 2),
+    _layer("f32", 1, 16, 24, 32, 24, 5, 2, 2, 2),
+    # stride 3: one launch per phase
+    _layer("bf16", 1, 24, 32, 24, 27, 3, 3), _layer("f32", 1, 9, 12, 24, 27, 3, 3),
+    # 1x1, 5x5, 7x7
+    _layer("bf16", 2, 72, 200, 13, 17, 1), _layer("bf16", 1, 281, 48, 9, 35, 1), _layer("f32", 2, 72, 40, 13, 17, 1),
+    _layer("bf16", 1, 40, 24, 30, 30, 5), _layer("f32", 1, 20, 40, 20, 30, 5), _layer("bf16", 1, 64, 9, 20, 28, 7),
+]
+
+
+def _run(L, x, w, dy):
+    p, nt = dc.Problem.of(L), L.P * L.Q
+    xt, dyt = H.alloc_tiles(p, X, nt, L.dtype), H.alloc_tiles(p, DY, nt, L.dtype)
+    H.scatter_interiors(xt, H.to_device(x, L.dtype), p, X)
+    H.scatter_interiors(dyt, H.to_device(dy, L.dtype), p, DY)
+    H.fill_halos_all_tiles(p, X, xt, L.dtype)
+    H.fill_halos_all_tiles(p, DY, dyt, L.dtype)
+    wd = H.to_device(w, L.dtype)
+    y = torch.full((nt, L.N, L.K, L.Hot, L.Wot), float("nan"), device="cuda")
+    dx = torch.full((nt, L.N, L.C, L.Ht, L.Wt), float("nan"), device="cuda")
+    dw = torch.full((L.K, L.C, L.R, L.S), float("nan"), device="cuda")
+    ws = torch.empty(max(dc.bwd_filter_workspace_bytes(p, ALL), 16), dtype=torch.uint8, device="cuda")
+    dc.conv_fwd(p, ALL, xt, wd, y)
+    dc.conv_bwd_data(p, ALL, dyt, wd, dx)
+    dc.conv_bwd_filter(p, ALL, xt, dyt, dw, 0, ws)
+    torch.cuda.synchronize()
+    return (H.gather_outputs(y, p, "y").cpu().numpy(), H.gather_outputs(dx, p, "dx").cpu().numpy(), dw.cpu().numpy())
+
+
+def _oracle(L, x, w, dy):
+    return (orc.round_f32(orc.conv_fwd(x, w, L.stride, L.pad)),
+            orc.round_f32(orc.conv_bwd_data(dy, w, L.H, L.W, L.stride, L.pad)),
+            orc.round_f32(orc.conv_bwd_filter(x, dy, L.R, L.S, L.stride, L.pad)))
+
+
+def _id(L):
+    return f"{L.dtype}-{L.N}x{L.C}-{L.K}-{L.H}x{L.W}-k{L.R}s{L.stride}-{L.P}x{L.Q}h{L.halo}"
+
+
+@pytest.mark.parametrize("L", LAYERS, ids=_id)
+def test_blocked_layer_matches_oracle(L):
+    print(f"[blocked] {L}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    for name, got, ref in zip(("y", "dx", "dw"), _run(L, x, w, dy), _oracle(L, x, w, dy)):
+        err = float(np.max(np.abs(got.astype(np.float64) - ref)) / np.max(np.abs(ref)))
+        assert np.all(np.isfinite(got)) and err <= 1e-5, (name, err)
+    x, w, dy = (wl.draw(L, t, dist="int") for t in ("x", "w", "dy"))
+    for name, got, ref in zip(("y", "dx", "dw"), _run(L, x, w, dy), _oracle(L, x, w, dy)):
+        assert np.array_equal(got, ref), name
+
+
+@pytest.mark.parametrize("L", [_layer("f32", 1, 40, 40, 12, 20, 3), _layer("f32", 1, 36, 24, 13, 10, 3, 2)], ids=_id)
+def test_fp32_extremes(L):
+    """Infinities and NaN reach the outputs that read them and no others; values near
+    both ends of the range keep fp32's accuracy."""
+    print(f"[extremes] {L}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    xi, dyi = x.copy(), dy.copy()
+    xi[0, 3, 5, 6], xi[0, 7, 2, 1], xi[0, 1, 9, 9] = np.inf, np.nan, -np.inf
+    dyi[0, 3, 1, 2], dyi[0, 9, 4, 3] = np.inf, np.nan
+    got, want = _run(L, xi, w, dyi), _oracle(L, x, w, dy)
+    t = [torch.from_numpy(np.ascontiguousarray(a)).double() for a in (xi, w, dyi)]
+    yi = torch.nn.functional.conv2d(t[0], t[1], stride=L.stride, padding=L.pad).numpy()
+    dxi = torch.nn.grad.conv2d_input(t[0].shape, t[1], t[2], L.stride, L.pad).numpy()
+    for name, g, ref, clean in (("y", got[0], yi, want[0]), ("dx", got[1], dxi, want[1])):
+        fin = np.isfinite(ref)
+        assert not fin.all() and np.array_equal(np.isnan(g), np.isnan(ref)), name
+        assert np.array_equal(g[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32)), name
+        assert float(np.max(np.abs(g[fin] - clean[fin])) / np.max(np.abs(clean))) <= 1e-5, name
+    for sx, sw in ((2.0 ** -122, 2.0 ** 20), (2.0 ** 120, 2.0 ** -20), (2.0 ** -60, 2.0 ** -50)):
+        xs, ws, ds = (np.ldexp(a.astype(np.float32), int(np.log2(s))) for a, s in ((x, sx), (w, sw), (dy, sx)))
+        y, dx, _ = _run(L, xs, ws, ds)
+        for name, g, clean in (("y", y, want[0]), ("dx", dx, want[1])):
+            # scaling by a power of two is exact but for inputs below 2^-126
+            e = np.max(np.abs(g.astype(np.float64) / (sx * sw) - clean)) / np.max(np.abs(clean))
+            assert e <= (1e-5 if sx > 2.0 ** -100 else 2e-5), (name, sx, e)
