@@ -148,4 +148,48 @@ __device__ __forceinline__ uint4 mask8(uint4 v, int nv) {
     return v;
 }
 
+// e / d for e, d < 2^16 by the host's m = 2^32 / d + 1 (0 for d = 1)
+__device__ __forceinline__ int div16(int e, uint32_t m) { return m ? int(__umulhi(uint32_t(e), m)) : e; }
+
+// What the three bf16 parts of a value cannot hold exactly: infinities, NaN,
+// magnitudes from 2^62 (their part products could overflow where the fp32
+// product does not) and nonzero ones below 2^-117 (the last part would lie
+// below bf16's range).  Tracked on the leading parts, two values a word:
+// `hi` their largest magnitudes, `lo` the smallest minus one (so that zero is
+// the largest).
+struct PartRange {
+    uint32_t hi = 0, lo = 0xffffffffu;
+    __device__ __forceinline__ bool outside() const {
+        return (hi & 0xffffu) >= 0x5e80u || (hi >> 16) >= 0x5e80u || (lo & 0xffffu) < 0x04ffu || (lo >> 16) < 0x04ffu;
+    }
+};
+
+// 8 fp32 values -> three records of bf16 parts (round to nearest, remainder,
+// again): each part holds 8 bits and a sign, so three hold all 24
+__device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], PartRange& range) {
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = f[2 * i], b = f[2 * i + 1];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf2));
+            if (s < 2) {
+                a -= __builtin_bit_cast(float, u << 16);
+                b -= __builtin_bit_cast(float, u & 0xffff0000u);
+            }
+            w[s][i] = u;
+        }
+        const us2 m = __builtin_bit_cast(us2, w[0][i] & 0x7fff7fffu);
+        range.hi = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, range.hi), m));
+        range.lo = __builtin_bit_cast(
+            uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, range.lo), us2(m - us2{1, 1})));
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s) p[s] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};
+}
+
 }  // namespace dc

@@ -478,7 +478,11 @@ bool igemm_plan(IgemmArgs& a, int dtype) {
         if (dtype == 1 && igemm_roll_plan(a)) return true;
         if (dtype == 1 && igemm_wreg_plan(a)) return true;
         if (dtype == 0 && igemm_f32w_plan(a)) return true;
-        if (igemm_tile_plan(a, dtype)) return true;
+        // what the chunked kernel cannot stage even by its smallest chunk (large
+        // strides) is refused, whichever kernel would run
+        if (lds_bytes_for(a, dtype, dtype == 1 ? 8 : 2, a.Cout <= 32 ? 32 : 64) <= device_lds_limit() &&
+            igemm_tile_plan(a, dtype))
+            return true;
     }
     a.OB = a.Cout <= 32 ? 32 : 64;
     // channel-chunk candidates, widest first: the channel count itself (rounded

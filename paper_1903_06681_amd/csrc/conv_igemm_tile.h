@@ -52,8 +52,6 @@ static constexpr int kTileWord3 = 0x00020000;   // buffer resource word 3 (gfx9 
 // Byte offset past every buffer here, whatever channel offset is added (the
 // plan keeps those below 2^31): such a load returns 0, such a store is dropped.
 static constexpr uint32_t kTileOut = 0x80000000u;
-// magnitudes above this could overflow in a part product while the fp32 product does not
-static constexpr float kTileBig = 4.611686e18f;   // 2^62
 
 // weight staging: per-element gathers (any layout); forward, a thread's 8
 // channels x T taps as T 16-byte loads; backward-data, 8 x 8 blocks
@@ -64,32 +62,6 @@ __host__ __device__ constexpr int tile_psu(int NS, int CCG) { return (NS * CCG) 
 // start in other banks, as a wave's writes go to several of them at once
 __host__ __device__ constexpr int tile_grec(int OB) { return OB + 1; }
 __host__ __device__ constexpr int tile_trec(int CCG, int OB) { return (CCG * tile_grec(OB)) | 1; }
-
-// e / d for e, d < 2^16 by the host's m = 2^32 / d + 1 (0 for d = 1)
-__device__ __forceinline__ int tile_div(int e, uint32_t m) { return m ? int(__umulhi(uint32_t(e), m)) : e; }
-
-// 8 fp32 values -> three records of bf16 parts; `bad` collects what the parts
-// do not hold, `mx` the largest magnitude
-__device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], uint32_t& bad, float& mx) {
-    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    uint32_t w[3][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float a = f[2 * i], b = f[2 * i + 1];
-        mx = fmaxf(mx, fmaxf(fabsf(a), fabsf(b)));
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf2));
-            a -= __builtin_bit_cast(float, u << 16);
-            b -= __builtin_bit_cast(float, u & 0xffff0000u);
-            w[s][i] = u;
-        }
-        bad |= __builtin_bit_cast(uint32_t, a) | __builtin_bit_cast(uint32_t, b);
-    }
-#pragma unroll
-    for (int s = 0; s < 3; ++s) p[s] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};
-}
 
 // element e of an array of 16-bit values held in 32-bit words
 template <int N>
@@ -181,7 +153,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
     const uint32_t pstep = uint32_t(plane) * ES;   // bytes per channel
     auto patch_unit = [&](int e, uint32_t& off, int& slot, int& lim) __attribute__((always_inline)) {
         const int cg = e % CCG, rest = e / CCG;
-        const int pr = tile_div(rest, a.tmpg), g = rest - pr * PG;
+        const int pr = div16(rest, a.tmpg), g = rest - pr * PG;
         const int gr = row0 + pr, gc = ca + g * GW;
         const bool in_lds = pr < PR, ok = in_lds & (gr < a.in_rows) & (gc < a.in_pitch);
         off = ok ? uint32_t(gr * a.in_pitch + gc) * ES + cg * 8 * pstep : kTileOut;
@@ -202,7 +174,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
     auto w_unit = [&](int e, uint32_t& off, int& slot, int& cg) __attribute__((always_inline)) {
         const bool in_lds = e < nwu;
         if constexpr (WM == kWGather) {
-            const int rest = tile_div(e, a.tmt), t = e - rest * T;
+            const int rest = div16(e, a.tmt), t = e - rest * T;
             const int o = a.wmode ? rest % OB : rest / CCG;
             cg = a.wmode ? rest / OB : rest % CCG;
             off = in_lds & (o0 + o < a.Cout) ? uint32_t(int((o0 + o) * a.w_os) + t) * ES + cg * 8 * wstep : kTileOut;
@@ -213,7 +185,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
             off = in_lds & (o0 + o < a.Cout) ? uint32_t((o0 + o) * int(a.w_os)) * ES + cg * 8 * wstep : kTileOut;
             slot = in_lds ? cg * GREC + o : -1;
         } else {
-            cg = tile_div(e, a.tmnf);
+            cg = div16(e, a.tmnf);
             const int f = (e - cg * NFG) * 8;
             off = in_lds & (o0 * T + f < a.Cout * T) ? uint32_t(o0 * T + f) * ES + cg * 8 * wstep : kTileOut;
             slot = in_lds ? f : -1;
@@ -231,8 +203,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
         for (int j = 0; j < 8; ++j)
             v[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rin, off + j * pstep, 0, 0));
     };
-    uint32_t bad = 0;
-    float mx = 0.f;
+    PartRange range;
     auto store_patch = [&](const uint4 (&v)[8], int slot, int lim) __attribute__((always_inline)) {
         if (slot < 0) return;
         const int step = PSU, odd = de ? (ROW / 2) * PSU : 0;
@@ -269,7 +240,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
             for (int i = 0; i < 4; ++i) {
                 const float g[8] = {f[0][i], f[1][i], f[2][i], f[3][i], f[4][i], f[5][i], f[6][i], f[7][i]};
                 uint4 p[3];
-                split8(g, p, bad, mx);
+                split8(g, p, range);
                 const int at = slot + (de ? (i / 2) * step + (i & 1) * odd : i * step);
 #pragma unroll
                 for (int s = 0; s < 3; ++s) pl[at + s * CCG] = p[s];
@@ -314,7 +285,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = __builtin_bit_cast(float, v[j]);
             uint4 p[3];
-            split8(f, p, bad, mx);
+            split8(f, p, range);
 #pragma unroll
             for (int s = 0; s < 3; ++s) wl[s * WPL + slot] = p[s];
         }
@@ -333,7 +304,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
             u32 d[8][4];
 #pragma unroll
             for (int j = 0; j < 8; ++j) { d[j][0] = v[j].x; d[j][1] = v[j].y; d[j][2] = v[j].z; d[j][3] = v[j].w; }
-            int o = tile_div(slot, a.tmt), t = slot - o * T;
+            int o = div16(slot, a.tmt), t = slot - o * T;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const u32 sel = (i & 1) ? 0x07060302u : 0x05040100u;
@@ -415,7 +386,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
 #pragma unroll
     for (int j = 0; j < NPBW; ++j) {
         const int p = min((wp * NPBW + j) * 32 + l32, np - 1);
-        const int ul = tile_div(p, a.tmbv), vl = p - ul * bv;
+        const int ul = div16(p, a.tmbv), vl = p - ul * bv;
         pix[j] = (ul * a.istr * ROW + (de ? vl : vl * a.istr)) * PSU;
     }
     const int abase = wo * 32 * NOBW + l32;
@@ -498,7 +469,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
     float* out = a.out + tile * a.out_tile + int64_t(n) * a.Cout * oplane;
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.Cout * oplane * 4, kTileWord3);
     if constexpr (NS == 3) {
-        if (__syncthreads_or(int(bad != 0 || mx > kTileBig))) {
+        if (__syncthreads_or(int(range.outside()))) {
             const float* inf = reinterpret_cast<const float*>(in);
             const float* wf = static_cast<const float*>(a.w);
             for (int e = tid; e < OB * np * NPH; e += kTileThreads) {
@@ -516,7 +487,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
 #pragma unroll
     for (int j = 0; j < NPBW; ++j) {
         const int p = (wp * NPBW + j) * 32 + l32;
-        const int ul = tile_div(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
+        const int ul = div16(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
         const bool live = (p < np) & (v < a.Vo);
 #pragma unroll
         for (int i = 0; i < NOBW; ++i) {

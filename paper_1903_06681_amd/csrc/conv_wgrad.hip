@@ -22,8 +22,10 @@
 // Partials are stored in MFMA fragment order (coalesced) and mapped back to
 // the dw layout by the reduction.
 //
-// Row kernels (general fallback: bf16 stride > 1, fp32): stage one output row
-// segment per step; partials in dw order.  fp32 uses v_mfma_f32_32x32x2_f32
+// Blocked kernel (conv_wgrad_tile.h): strides above 1, narrow images, fp32 of
+// more than 32 channels.  Row kernels (the smallest fp32 layers, and samples
+// past the blocked kernel's 32-bit byte offsets): stage one output row segment
+// per step; partials in dw order.  fp32 uses v_mfma_f32_32x32x2_f32
 // with flattened (ci, r, s) columns in blocks of 32.
 #include <hip/hip_runtime.h>
 
@@ -35,6 +37,8 @@
 #include "kernels.h"
 
 namespace dc {
+
+hipError_t launch_wgrad_tile(const WgradArgs& a, int dtype, hipStream_t s);
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
@@ -68,6 +72,7 @@ struct Plan {
     int nqb, nseg, rows_per_seg;
     int64_t F;
     int frag;
+    WgradTile tile;
 };
 
 // tap-split kernel: square filters whose R*S taps spread over four waves fit
@@ -130,9 +135,44 @@ static int f32w_lds(int C, int R, int S) {
     return ring > red ? ring : red;
 }
 
+// LDS of the row kernels: a step's dy rows and the x rows of its columns
+static int64_t rows_lds(int dtype, int C, int R, int S, int istr) {
+    if (dtype == 1) return (64 * kDyP + 64 * int64_t(odd16(std::min(bf16_trb(S), R) * bf16_xwp(istr, S)))) * 2;
+    const int64_t XW = int64_t(kBQ - 1) * istr + S;
+    const int span = std::min(C, 256 / (R * S) + 2);   // channels 256 flattened columns can touch
+    return (64 * (kBQ + 1) + span * R * XW) * 4;
+}
+
 static bool make_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, int stride,
                       int Hot, int Wot, int base_c, int dy_off, Plan* pl) {
     std::memset(pl, 0, sizeof(*pl));
+    // what the row kernels cannot stage (filters over 7 wide in bf16, strides of
+    // about 7 and more) is refused, whichever kernel would run
+    const bool stageable = !(dtype == 1 && S > 7) && rows_lds(dtype, C, R, S, stride) <= device_lds_limit();
+    auto blocked = [&]() {
+        if (!stageable) return false;
+        if (!wgrad_tile_plan(dtype, ntiles, N, C, K, R, S, stride, Hot, Wot, base_c, dy_off, &pl->tile)) return false;
+        pl->kind = WGRAD_TILE;
+        pl->gy = pl->tile.gy; pl->gz = pl->tile.gz; pl->nchunks = pl->tile.nchunks; pl->F = pl->tile.F;
+        pl->nqb = pl->tile.nqb;
+        pl->frag = 6;
+        return true;
+    };
+    const int64_t pixels = int64_t(ntiles) * N * Hot * Wot;
+    // Narrow images in bf16: a 64-column strip leaves most of its columns empty,
+    // flattened blocks do not (3x3, 256 channels, 14x14, N=32: 58 -> 32 us; 128
+    // channels, 7x7: 21 -> 16; at 56 columns the strips win, 25 against 32, as
+    // their rows are staged once).  With at most 32 channels both ways the strips
+    // keep up from 14 columns on, and on a few hundred pixels (11 against 12 us).
+    // 1x1: strips read x and dy once per 64 x 64 block, 128-wide blocks half as
+    // often (512 -> 128, 28x28, N=16: 28 -> 20 us; 56x56, N=1: 12 against 14).
+    if (dtype == 1 && stride == 1) {
+        const bool wide = C > 32 || K > 32;
+        if (R * S == 1 ? C > 64 && K > 64 && Wot <= 56 && pixels >= 4096
+                       : pixels >= 1024 && (Wot <= 8 || (wide && Wot <= 32))) {
+            if (blocked()) return true;
+        }
+    }
     const bool xcol_aligned = base_c % 8 == 0;   // strip staging reads whole 16-byte x chunks
     const bool phase2 = dtype == 1 && stride == 2 && 4 * C <= 32 && xcol_aligned && taps2_filter(R, S);
     if ((dtype == 1 && stride == 1 && S <= 7 && xcol_aligned) || phase2) {
@@ -199,6 +239,12 @@ static bool make_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, 
         pl->frag = 4;
         return true;
     }
+    // The blocked kernel's three bf16 parts and its reduction cost about 2 us more
+    // than the fp32 row kernel's short chain on the smallest layers (3x3 stride 2:
+    // 3 -> 16 channels on a 64x64 tile 11 against 13 us, 64 -> 64 on 16x16 16 against
+    // 19; 32 -> 32 on 512x512 105 -> 34).
+    const bool few = dtype == 0 && (pixels <= 256 || (int64_t(K) * C * R * S <= 2304 && pixels <= 16384));
+    if (!few && blocked()) return true;
     if (dtype == 1) {
         if (S > 7) return false;
         pl->kind = WGRAD_ROWS_BF16;
@@ -239,7 +285,14 @@ bool wgrad_plan(WgradArgs& a, int dtype) {
     a.chunks_per_tile = pl.chunks_per_tile; a.rows_per_chunk = pl.rows_per_chunk;
     a.nqb = pl.nqb; a.nseg = pl.nseg; a.rows_per_seg = pl.rows_per_seg;
     a.F = pl.F; a.frag = pl.frag;
-    if (a.kind == WGRAD_F32W) {
+    if (a.kind == WGRAD_TILE) {
+        const WgradTile& t = pl.tile;
+        a.tcfg = t.tcfg; a.tnow = t.now; a.tncw = t.ncw; a.two = t.wo; a.twc = t.wc; a.ttw = t.tw; a.tnws = t.nws;
+        a.tbu = t.tbu; a.tbv = t.tbv; a.tnub = t.tnub; a.tnpb = t.tnpb; a.tbpc = t.tbpc;
+        a.tpg = t.tpg; a.tdg = t.tdg; a.tnbuf = t.tnbuf;
+        a.tmpg = t.tmpg; a.tmdg = t.tmdg; a.tmbv = t.tmbv;
+        a.lds_bytes = t.lds_bytes;
+    } else if (a.kind == WGRAD_F32W) {
         a.lds_bytes = f32w_lds(f32w_class(a.C), a.R, a.S);
     } else if (a.kind == WGRAD_KSLICE_BF16) {
         // the staging buffers; after the loop the waves' sums (NW/2 of them at once)
@@ -249,14 +302,10 @@ bool wgrad_plan(WgradArgs& a, int dtype) {
     } else if (a.kind == WGRAD_STRIP_BF16 || a.kind == WGRAD_TAPS_BF16 || a.kind == WGRAD_TAPS2_BF16) {
         const int cb = a.kind == WGRAD_STRIP_BF16 ? 64 : 32;
         a.lds_bytes = ((a.TRB + 1) * cb * kXP + 2 * cb * kXP) * 2;
-    } else if (a.kind == WGRAD_ROWS_BF16) {
-        const int plane = odd16(a.TRB * bf16_xwp(a.istr, a.S));
-        a.lds_bytes = (64 * kDyP + 64 * plane) * 2;
     } else {
-        const int XW = (kBQ - 1) * a.istr + a.S;
-        // channels a workgroup's 256 flattened columns can touch
-        const int span = std::min(a.C, 256 / (a.R * a.S) + 2);
-        a.lds_bytes = (64 * (kBQ + 1) + span * a.R * XW) * 4;
+        const int64_t lds = rows_lds(dtype, a.C, a.R, a.S, a.istr);
+        if (lds > device_lds_limit()) return false;
+        a.lds_bytes = int(lds);
     }
     return a.lds_bytes <= device_lds_limit();
 }
@@ -1604,6 +1653,7 @@ static hipError_t launch_rows_bf16(const WgradArgs& a, dim3 grid, hipStream_t s)
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, int dtype, hipStream_t s) {
+    if (a.kind == WGRAD_TILE) return launch_wgrad_tile(a, dtype, s);
     dim3 grid(a.nchunks, a.gy, a.gz);
     hipError_t e = hipErrorInvalidValue;
     if (a.kind == WGRAD_STRIP_BF16) {

@@ -136,7 +136,22 @@ hipError_t launch_igemm_frame(const IgemmArgs& a, int dtype, hipStream_t s);
 // summed over the chunk's (n, p, q).
 
 enum WgradKind { WGRAD_STRIP_BF16 = 0, WGRAD_ROWS_BF16 = 1, WGRAD_ROWS_F32 = 2, WGRAD_TAPS_BF16 = 3,
-                 WGRAD_TAPS2_BF16 = 4, WGRAD_F32W = 5, WGRAD_KSLICE_BF16 = 6 };
+                 WGRAD_TAPS2_BF16 = 4, WGRAD_F32W = 5, WGRAD_KSLICE_BF16 = 6, WGRAD_TILE = 7 };
+
+// Plan of the blocked weight gradient: instantiation (32x32 blocks per wave
+// now x ncw, waves wo x wc x taps, tw taps per wave; nws waves hold sums at
+// the end), pixel blocks of tbu x tbv (tnub x nqb per image, tnpb in all, tbpc
+// per chunk), 16-byte vectors per staged x and dy row, staging buffers, and
+// 2^32 / d + 1 of the kernel's divisors (0 for 1).
+struct WgradTile {
+    int tcfg, now, ncw, wo, wc, tw, nws;
+    int tbu, tbv, tnub, nqb, tnpb, tbpc, tpg, tdg, tnbuf;
+    int gy, gz, nchunks, lds_bytes;
+    int64_t F;
+    uint32_t tmpg, tmdg, tmbv;
+};
+bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, int st, int Hot, int Wot,
+                     int base_c, int dy_off, WgradTile* t);
 
 struct WgradArgs {
     const void* x;               // padded x tiles
@@ -163,9 +178,16 @@ struct WgradArgs {
     int frag;                    // 0: partials in dw order; 1 .. 5: in MFMA fragment order (64x64
                                  // blocks, 32x32 blocks, 32x32 blocks of stride-2 phase images,
                                  // fp32 32 filters x 32 flattened (ci, r, s), 32x32 blocks as
-                                 // float4 per lane)
+                                 // float4 per lane; 6: the blocked kernel's)
     int lds_bytes;
+    // blocked kernel (WgradTile)
+    int tcfg, tnow, tncw, two, twc, ttw, tnws;
+    int tbu, tbv, tnub, tnpb, tbpc, tpg, tdg, tnbuf;
+    uint32_t tmpg, tmdg, tmbv;
 };
+
+hipError_t launch_wgrad_tile_bf16(const WgradArgs& a, hipStream_t s);
+hipError_t launch_wgrad_tile_f32(const WgradArgs& a, hipStream_t s);
 
 size_t wgrad_workspace_bytes(int dtype, int ntiles, int N, int C, int K, int R, int S,
                              int stride, int Hot, int Wot, int base_c, int dy_off);
