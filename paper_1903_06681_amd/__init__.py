@@ -119,9 +119,18 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The current stream's handle without building a Stream object: a call of a
+# small layer takes 7 us on the host, 2.8 of them in current_stream().  torch
+# keeps one current stream per device; builds without these two bindings (or
+# without a GPU) take the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
-        import torch
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
