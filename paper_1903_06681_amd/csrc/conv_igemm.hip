@@ -465,6 +465,38 @@ void igemm_set_frame(IgemmArgs& a, const int bands[4]) {
     }
 }
 
+// Stride-1 layers that a register-weight kernel takes too, but the blocked
+// kernel runs faster (us, register weights against blocked).  The rule reads
+// one tile's sizes only, so that a tile's outputs do not depend on how many
+// tiles a launch has.
+static bool prefer_blocked(const IgemmArgs& a, int dtype) {
+    if (a.istr != 1 || a.ostr != 1) return false;
+    const int T = a.Tr * a.Ts;
+    if (dtype == 0) {
+        // fp32 3x3: two channels per fp32 matrix instruction against sixteen per six
+        // bf16 ones, once the channels fill them (512x512 tile: 32 -> 18 channels 51
+        // against 36, 32 -> 32 62 against 41, 18 -> 32 36 against 39), or once several
+        // 32-filter blocks each walk the input again (16 -> 128: 104 against 90).  1x1
+        // is all staging, which the parts make dearer (16 against 20).
+        return T > 1 && (a.Cin > 18 || (a.Cin > 8 && a.Cout > 64));
+    }
+    const int64_t out_bytes = int64_t(a.Nn) * a.Cout * a.out_rows * a.out_cols * 4;
+    if (T == 1) {
+        // Large outputs: whole lines leave through the L2 instead of 4-byte device-scope
+        // stores (64 -> 256 on 56x56, N=32: 61 against 39; 256 -> 64: 24 against 19, on
+        // 28x28: 15 against 16).  More than 64 channels both ways: each 64-filter block
+        // would read the input again (256 -> 128: 54 against 37).  Rows under 16
+        // columns: no empty strip columns (10.4 against 8.6).
+        return a.Vo < 16 || (a.Cin > 64 && a.Cout > 64) || out_bytes >= (int64_t(24) << 20) ||
+               (a.Cout > 64 && out_bytes >= (int64_t(8) << 20));
+    }
+    // 3x3 forward on narrow images: flattened pixels against strips with empty columns
+    // (14x14, N=32: 64 -> 96 12 against 9, 64 -> 256 16 against 12; 28x28 64 -> 256 17
+    // against 15, 64 -> 96 equal).  Backward-data stages its weights through 8 x 8
+    // transposes and does not gain (9.0 against 10.1).
+    return a.wmode == 0 && ((a.Vo <= 16 && a.Cout > 32) || (a.Vo <= 32 && a.Cout > 128));
+}
+
 bool igemm_plan(IgemmArgs& a, int dtype) {
     a.kind = 0;
     // a merged-phase backward-data request runs on the register-weight kernel or not at all
@@ -474,15 +506,18 @@ bool igemm_plan(IgemmArgs& a, int dtype) {
     // a frame runs on the frame kernel, else on the chunked kernel (the strip
     // kernels cover whole tiles)
     if (a.frame && igemm_frame_plan(a, dtype)) return true;
+    // what the chunked kernel cannot stage even by its smallest chunk (large
+    // strides) is refused, whichever kernel would run
+    auto blocked = [&]() {
+        return lds_bytes_for(a, dtype, dtype == 1 ? 8 : 2, a.Cout <= 32 ? 32 : 64) <= device_lds_limit() &&
+               igemm_tile_plan(a, dtype);
+    };
     if (!a.frame) {
+        if (prefer_blocked(a, dtype) && blocked()) return true;
         if (dtype == 1 && igemm_roll_plan(a)) return true;
         if (dtype == 1 && igemm_wreg_plan(a)) return true;
         if (dtype == 0 && igemm_f32w_plan(a)) return true;
-        // what the chunked kernel cannot stage even by its smallest chunk (large
-        // strides) is refused, whichever kernel would run
-        if (lds_bytes_for(a, dtype, dtype == 1 ? 8 : 2, a.Cout <= 32 ? 32 : 64) <= device_lds_limit() &&
-            igemm_tile_plan(a, dtype))
-            return true;
+        if (blocked()) return true;
     }
     a.OB = a.Cout <= 32 ? 32 : 64;
     // channel-chunk candidates, widest first: the channel count itself (rounded

@@ -52,6 +52,7 @@ static constexpr int kTileWord3 = 0x00020000;   // buffer resource word 3 (gfx9 
 // Byte offset past every buffer here, whatever channel offset is added (the
 // plan keeps those below 2^31): such a load returns 0, such a store is dropped.
 static constexpr uint32_t kTileOut = 0x80000000u;
+static constexpr int kTileNT = 2;               // a buffer store's non-temporal bit
 
 // weight staging: per-element gathers (any layout); forward, a thread's 8
 // channels x T taps as T 16-byte loads; backward-data, 8 x 8 blocks
@@ -102,9 +103,12 @@ hipError_t launch_tile_f32(const IgemmArgs& a, hipStream_t s);
 // staging and its taps (kWRows); WPT, UPT: weight and patch units per thread
 // held in registers; BP: the four output phases of a stride-2 backward-data
 // together (each tap belongs to one phase; the input patch is shared and the
-// two column phases leave as 8-byte stores).
-template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP>
-__global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a) {
+// two column phases leave as 8-byte stores).  KG: groups of four waves that
+// take the channel chunks in turn, each with its own staging buffers, and are
+// added at the end: twice the waves per SIMD and half the chain where a layer
+// has too few blocks for two workgroups per CU.
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG>
+__global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     static_assert(WO * WP == 4, "four waves");
     static_assert(NS == 1 || WM == kWGather, "fp32 weights are gathered");
@@ -127,7 +131,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
     const int bu = min(a.tbu, a.Uo - u0), bv = a.tbv;   // columns past Vo: computed, not stored
     const int o0 = ob * OB;
     const int T = a.R * a.S;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kTileThreads) : 0;
+    const int tid = threadIdx.x % kTileThreads, wave = tid >> 6, lane = tid & 63;
     const int l32 = lane & 31, hi = lane >> 5;
     const int wo = wave / WP, wp = wave % WP;
 
@@ -138,7 +143,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void*>(a.w), 0, a.wK * a.wC * T * ES, kTileWord3);
 
-    uint4* wl = reinterpret_cast<uint4*>(smem);   // [NS][T][CCG][OB], a record of pad per tap
+    uint4* wl = reinterpret_cast<uint4*>(smem) + kg * a.tgrec;   // [NS][T][CCG][OB], padded
     uint4* pl = wl + NS * T * TREC;               // [PR][ROW][PSU]
     const int WPL = T * TREC;
     const int PG = a.tpg, PR = (bu - 1) * a.istr + a.Tr;   // 8-pixel groups per row, rows
@@ -425,12 +430,16 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
     };
 
     const int cin = a.Tr > 0 ? a.Cin : 0;   // an output phase without taps is zero
-    if (cin > 0) load_chunk(0);
-    for (int c0 = 0; c0 < cin; c0 += CC) {
-        if (c0 > 0) __syncthreads();
-        store_chunk(c0);
+    constexpr int STEP = KG * CC;
+    if (kg * CC < cin) load_chunk(kg * CC);
+    for (int c1 = 0; c1 < cin; c1 += STEP) {
+        const int c0 = c1 + kg * CC;
+        const bool mine = KG == 1 || c0 < cin;
+        if (c1 > 0) __syncthreads();
+        if (mine) store_chunk(c0);
         __syncthreads();
-        if (c0 + CC < cin) load_chunk(c0 + CC);
+        if (c0 + STEP < cin) load_chunk(c0 + STEP);
+        if (!mine) continue;
         const int ng = min(CCG, (a.Cin - c0 + 7) / 8);   // channel groups of this chunk
 #pragma unroll
         for (int ph = 0; ph < NPH; ++ph) {
@@ -472,7 +481,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
         if (__syncthreads_or(int(range.outside()))) {
             const float* inf = reinterpret_cast<const float*>(in);
             const float* wf = static_cast<const float*>(a.w);
-            for (int e = tid; e < OB * np * NPH; e += kTileThreads) {
+            for (int e = threadIdx.x; e < OB * np * NPH; e += kTileThreads * KG) {
                 const int p = e % np, rest = e / np;
                 const int ph = rest % NPH, o = o0 + rest / NPH;
                 const int ul = p / bv, u = u0 + ul, v = v0 + p - ul * bv;
@@ -484,6 +493,35 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
             return;
         }
     }
+    if constexpr (KG > 1) {
+        // group 1's sums to LDS, added by group 0
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        constexpr int NT = NPH * NOBW * NPBW;
+        f32x4* red = reinterpret_cast<f32x4*>(smem) + wave * NT * 256 + lane;
+        __syncthreads();
+        if (kg == 1) {
+            static_for<0, NT>([&](auto tc) __attribute__((always_inline)) {
+                constexpr int t = decltype(tc)::value;
+                const floatx16& v = acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) red[(t * 4 + q) * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+            });
+        }
+        __syncthreads();
+        if (kg == 1) return;
+        static_for<0, NT>([&](auto tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value;
+            floatx16& v = acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 f = red[(t * 4 + q) * 64];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[4 * q + j] += f[j];
+            }
+        });
+    }
+    auto finish = [&](auto ntc) __attribute__((always_inline)) {
+    constexpr int AUX = decltype(ntc)::value;
 #pragma unroll
     for (int j = 0; j < NPBW; ++j) {
         const int p = (wp * NPBW + j) * 32 + l32;
@@ -504,8 +542,8 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
                         const float f0 = acc[2 * py][i][j][e], f1 = acc[2 * py + 1][i][j][e];
                         typedef u32 u32x2 __attribute__((ext_vector_type(2)));
                         const u32x2 w2 = {__builtin_bit_cast(u32, f0), __builtin_bit_cast(u32, f1)};
-                        __builtin_amdgcn_raw_buffer_store_b64(w2, rout, ok & both & (o < a.Cout) ? off : kTileOut, 0, 0);
-                        if (!both & ok & (o < a.Cout)) __builtin_amdgcn_raw_buffer_store_b32(w2[0], rout, off, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b64(w2, rout, ok & both & (o < a.Cout) ? off : kTileOut, 0, AUX);
+                        if (!both & ok & (o < a.Cout)) __builtin_amdgcn_raw_buffer_store_b32(w2[0], rout, off, 0, AUX);
                     }
                 }
             } else {
@@ -516,22 +554,25 @@ __global__ __launch_bounds__(kTileThreads, 2) void igemm_tile_kernel(IgemmArgs a
                     const uint32_t off = (o * oplane + orow * a.out_cols + ocol) * 4;
                     const float f = acc[0][i][j][e];
                     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, f), rout,
-                                                          live & (o < a.Cout) ? off : kTileOut, 0, 0);
+                                                          live & (o < a.Cout) ? off : kTileOut, 0, AUX);
                 }
             }
         }
     }
+    };
+    if (a.nt) finish(std::integral_constant<int, kTileNT>{});
+    else finish(std::integral_constant<int, 0>{});
 }
 
-template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP>
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG = 1>
 static hipError_t launch_tile(const IgemmArgs& a, hipStream_t s) {
-    auto k = igemm_tile_kernel<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP>;
+    auto k = igemm_tile_kernel<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG>;
     if (a.lds_bytes > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k, dim3((a.tnpb + 7) / 8 * 8 * a.tnob), dim3(kTileThreads), a.lds_bytes, s, a);
+    hipLaunchKernelGGL(k, dim3((a.tnpb + 7) / 8 * 8 * a.tnob), dim3(kTileThreads * KG), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 

@@ -47,10 +47,22 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
     const int groups = (a.Cin + 7) / 8;
     const int taps = a.bp ? T : a.Tr * a.Ts;
     const double ksteps = double(taps) * groups / 2.0 / nchunk;   // per chunk
+    // Two groups of waves on the chunks where one tile's nominal 64 x 128 blocks
+    // leave CUs without a second workgroup and there are chunks to share (fp32
+    // 128 -> 128 on a 64x64 tile: 42 -> 29 us; bf16 256 -> 256 stride 2 on 28x28,
+    // N=32: 34 -> 25).  The four phases of a stride-2 backward-data make four times
+    // the outputs of a block: at 256 blocks one group is faster (31 against 40).
+    // The rule reads one tile's sizes only: the order of the sums does not depend
+    // on how many tiles a launch has.
+    const int64_t nominal = int64_t(a.Nn) * ((int64_t(a.Uo) * a.Vo + 127) / 128) * ((a.Cout + 63) / 64);
+    const bool pair = nominal <= (a.bp ? cus / 2 : cus) && nchunk >= 4 &&
+                      (NS == 3 ? ccg == 2 : ccg == 4 && (wm == kWBlocks || (wm == kWRows && T == 9)));
     double best = 0;
     bool found = false;
+    for (int kg = pair ? 2 : 1; kg >= 1 && !found; --kg)
     for (int c = 0; c < nc; ++c) {
         const Cfg& f = cfgs[c];
+        if (kg == 2 && NS == 1 && !a.bp && (f.id == 0 || f.id == 4)) continue;
         if (wm == kWGather && NS == 1 && !a.bp && (f.id == 0 || f.id == 4)) continue;
         const int nob = (a.Cout + f.OB - 1) / f.OB;
         const int nv0 = (a.Vo + f.PT - 1) / f.PT, nv1 = std::min((a.Vo + 7) / 8, nv0 + 31);
@@ -66,17 +78,19 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
             const int shm = (bv * a.istr) % GW == 0 || nvb == 1 ? a.base_c % GW : GW - 1;
             const int pg = (shm + (bv - 1) * a.istr + std::max(a.Ts, 1) + GW - 1) / GW;
             const int pr = (bu - 1) * a.istr + a.Tr;
-            const int64_t lds = (int64_t(NS) * T * tile_trec(ccg, f.OB) + int64_t(pr) * pg * GW * tile_psu(NS, ccg)) * 16;
+            const int64_t grec = int64_t(NS) * T * tile_trec(ccg, f.OB) + int64_t(pr) * pg * GW * tile_psu(NS, ccg);
+            const int64_t sums = kg == 2 ? int64_t(a.bp ? 4 : 1) * f.NOBW * f.NPBW * 4 * 4096 : 0;
+            const int64_t lds = std::max(grec * 16 * kg, sums);
             if (lds > limit) continue;
             const int occ = lds * 2 <= limit ? 2 : 1;
             const int64_t npb = images * nub * nvb;
             if ((npb + 8) * nob > (int64_t(1) << 30)) continue;
             const int64_t nwg = npb * nob;
             const double mf = ksteps * f.NOBW * f.NPBW * (NS == 3 ? 6 : 1) * 32.0;
-            const double stage = 700.0 + double(lds) / 48.0 * (NS == 3 ? 1.5 : 1.0);
+            const double stage = 700.0 + double(grec) / 3.0 * (NS == 3 ? 1.5 : 1.0);
             const int64_t slots = int64_t(cus) * occ;
-            const int k = int(std::min<int64_t>(occ, (nwg + cus - 1) / cus));
-            const double per = nchunk * std::max(k * mf, mf + stage) + 4000.0;
+            const int k = kg * int(std::min<int64_t>(occ, (nwg + cus - 1) / cus));
+            const double per = double((nchunk + kg - 1) / kg) * std::max(k * mf, mf + stage) + 4000.0 + (kg - 1) * 1500.0;
             const double cost = per * double((nwg + slots - 1) / slots);
             if (!found || cost < best) {
                 found = true;
@@ -85,6 +99,14 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
                 a.tbu = bu; a.tbv = bv; a.tnub = nub; a.nvb = nvb;
                 a.tpg = pg; a.tnpb = int(npb);
                 a.lds_bytes = int(lds);
+                a.tkg = kg; a.tgrec = int(grec);
+                // whole 64-byte sectors of a large output bypass the caches (64 -> 256 1x1
+                // on 56x56, N=32, 103 MB: 39 -> 25 us; with blocks of 196 pixels, whose
+                // sectors are shared, on 28x28: 14 -> 24)
+                const bool rows = a.out_cols % 16 == 0 && bv % 16 == 0;
+                const bool flat = !a.bp && a.ostr == 1 && nvb == 1 && (int64_t(a.out_rows) * a.out_cols) % 16 == 0 &&
+                                  int64_t(bu) * bv % 16 == 0;
+                a.nt = (rows || flat) && int64_t(a.Nn) * a.Cout * a.out_rows * a.out_cols * 4 >= (int64_t(8) << 20);
             }
         }
     }

@@ -11,6 +11,11 @@ hipError_t launch_tile_bf16(const IgemmArgs& a, hipStream_t s) {
 #define X(id, nob, npb, wo, wp) \
     if (a.tcfg == id) { \
         constexpr int OB = 32 * nob * wo; \
+        if constexpr (id >= 1 && id <= 3) { \
+            if (a.tkg == 2 && a.twm == kWRows && T == 9 && a.tccg == 4) return launch_tile<1, 4, nob, npb, wo, wp, kWRows, 9, (OB + 63) / 64, 1, false, 2>(a, s); \
+            if (a.tkg == 2 && a.twm == kWBlocks && a.tccg == 4) return launch_tile<1, 4, nob, npb, wo, wp, kWBlocks, 1, OB == 32 ? 1 : 2, 1, false, 2>(a, s); \
+        } \
+        if (a.tkg != 1) return hipErrorInvalidValue; \
         if (a.twm == kWRows && T == 9 && a.tccg == 4) return launch_tile<1, 4, nob, npb, wo, wp, kWRows, 9, (OB + 63) / 64, 2, false>(a, s); \
         if (a.twm == kWRows && T == 1 && a.tccg == 8) return launch_tile<1, 8, nob, npb, wo, wp, kWRows, 1, (OB + 31) / 32, 2, false>(a, s); \
         if (a.twm == kWBlocks && a.tccg == 2) return launch_tile<1, 2, nob, npb, wo, wp, kWBlocks, 1, 2, 1, false>(a, s); \

@@ -38,12 +38,19 @@ __device__ __forceinline__ void wreg_store(float* p, float v) {
 // channel), added to the row's offset; the lane's part is voff.  Written as
 // a 64-bit address expression, the per-channel offsets stayed live, ran the
 // kernel out of scalar registers and were read back from lanes of a vector
-// register (v_readlane) in front of every store.
-template <int OC>
+// register (v_readlane) in front of every store.  NT: non-temporal, for the
+// stride-2 forward, whose output is many times its input (conv1 at 224^2,
+// N = 32, 103 MB, buffers changing from call to call: 62 -> 45 us; the 3x3
+// and 1x1 layers that stay on this kernel gain nothing or lose 0.4 us).
+template <int OC, bool NT>
 __device__ __forceinline__ void wreg_store_oc(__amdgpu_buffer_rsrc_t rs, int voff, int rowoff, int cstride, float v) {
     int so;
-    asm volatile("s_mul_i32 %0, %1, %2\n\ts_add_i32 %0, %0, %3\n\tbuffer_store_dword %4, %5, %6, %0 offen sc1"
-                 : "=&s"(so) : "s"(cstride), "n"(OC), "s"(rowoff), "a"(v), "v"(voff), "s"(rs));
+    if constexpr (NT)
+        asm volatile("s_mul_i32 %0, %1, %2\n\ts_add_i32 %0, %0, %3\n\tbuffer_store_dword %4, %5, %6, %0 offen nt"
+                     : "=&s"(so) : "s"(cstride), "n"(OC), "s"(rowoff), "a"(v), "v"(voff), "s"(rs));
+    else
+        asm volatile("s_mul_i32 %0, %1, %2\n\ts_add_i32 %0, %0, %3\n\tbuffer_store_dword %4, %5, %6, %0 offen sc1"
+                     : "=&s"(so) : "s"(cstride), "n"(OC), "s"(rowoff), "a"(v), "v"(voff), "s"(rs));
 }
 
 static constexpr int kWThreads = 256;
@@ -449,9 +456,9 @@ __global__ __launch_bounds__(kWThreads, MINWG) void igemm_wreg_kernel(IgemmArgs 
             const __amdgpu_buffer_rsrc_t rs = rout;
             const int vo = voff_out, ro = prow4, cs = opl4;
             if constexpr (MF) {
-                if (v < a.Vo) wreg_store_oc<oc>(rs, vo, ro, cs, prev[sob][e]);
+                if (v < a.Vo) wreg_store_oc<oc, PH>(rs, vo, ro, cs, prev[sob][e]);
             } else {
-                wreg_store_oc<oc>(rs, vo, ro, cs, prev[sob][e]);
+                wreg_store_oc<oc, PH>(rs, vo, ro, cs, prev[sob][e]);
             }
         };
         auto mfmas = [&](auto with_stores) {

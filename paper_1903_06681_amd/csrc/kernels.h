@@ -93,6 +93,8 @@ struct IgemmArgs {
     // (tnub block rows x nvb block columns per image, tnpb in all), 16-byte
     // vectors per patch row
     int tcfg, tccg, twm, tnob, tnpb, tbu, tbv, tnub, tpg;
+    int tkg, tgrec;              // groups of waves that share the channel chunks (1 or 2), their LDS records
+    int nt;                      // outputs leave by non-temporal stores (blocked, rolling-row kernels)
     uint32_t tmt, tmpg, tmbv, tmnf;   // 2^32 / d + 1 of the kernel's divisors (0 for 1)
     int nvb, nseg, rows_per_seg; // strip kernels: 64- (128-, rolling) column strips, row segments
     // frame mode (chunked and frame kernels): the launch covers only the
