@@ -173,6 +173,11 @@ static bool make_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, 
             if (blocked()) return true;
         }
     }
+    // fp32 3x3 of 19 to 32 channels: the flattened-column kernel walks x once per 32
+    // filters on the fp32 matrix instruction; over enough pixels to hide the blocked
+    // kernel's longer start its bf16 parts are faster (512x512 tile: 32 -> 32 60
+    // against 56 us, 32 -> 64 114 against 92; on 256x256 27 against 29).
+    if (dtype == 0 && stride == 1 && R * S > 1 && C > 18 && pixels >= 131072 && blocked()) return true;
     const bool xcol_aligned = base_c % 8 == 0;   // strip staging reads whole 16-byte x chunks
     const bool phase2 = dtype == 1 && stride == 2 && 4 * C <= 32 && xcol_aligned && taps2_filter(R, S);
     if ((dtype == 1 && stride == 1 && S <= 7 && xcol_aligned) || phase2) {

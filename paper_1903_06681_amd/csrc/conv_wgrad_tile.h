@@ -426,4 +426,8 @@ static hipError_t launch_wgrad_tile(const WgradArgs& a, hipStream_t s) {
     X(9, 2, 2, 2, 1, 1, 4, 1)  /* 128 x 64, one tap */ \
     X(10, 1, 1, 2, 2, 2, 1, 7) /* 64 x 64, fourteen taps */
 
+// Pixels of a block: 128, in fp32 64 where the operands are wider than 32 (three
+// parts of two buffers of 128 do not fit the LDS).
+constexpr int wt_pixels(int NS, int id) { return NS == 1 || id == 3 ? 128 : 64; }
+
 }  // namespace dc

@@ -16,7 +16,7 @@ const Cfg kCfgs[] = {DC_WT_CONFIGS(X)};
 
 bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, int st, int Hot, int Wot,
                      int base_c, int dy_off, WgradTile* t) {
-    const int NS = dtype == 1 ? 1 : 3, ES = dtype == 1 ? 2 : 4, GW = 16 / ES, P = dtype == 1 ? 128 : 64;
+    const int NS = dtype == 1 ? 1 : 3, ES = dtype == 1 ? 2 : 4, GW = 16 / ES;
     const int T = R * S;
     if (base_c < 0) return false;
     // byte offsets within a sample are 32-bit, with room for a block's channels past the
@@ -32,6 +32,7 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
     else if (T <= 28) id = NS == 1 && !k32 && !c32 ? 10 : 4;
     else id = 5;
     const Cfg& f = kCfgs[id];
+    const int P = wt_pixels(NS, id);
     const int OBK = 32 * f.now * f.wo, CBK = 32 * f.ncw * f.wc, NOB = OBK / 32, NCB = CBK / 32;
     const int limit = device_lds_limit();
     const int nws = f.wo * f.wc * f.wt, nbw = f.tw * f.now * f.ncw;
@@ -60,7 +61,10 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
             const int ks = (bu * bv + 15) / 16;
             const double mf = double((ks + f.wk - 1) / f.wk) * std::min(T, f.tw) * f.now * f.ncw * (NS == 3 ? 6 : 1) * 64.0;
             const double stage = (double(pr) * pg * GW * CBK + double(bu) * dg * GW * OBK) * (NS == 3 ? 0.09 : 0.035);
-            const double cost = double(npb) * (mf + stage + (nbuf == 2 ? 400.0 : 900.0));
+            // staging units past one per thread are loaded without being requested ahead
+            const int units = ((bu * dg * OBK / 8 + 63) & ~63) + pr * pg * CBK / 8;
+            const double late = NS == 3 && units > kWtThreads ? 1500.0 : 0.0;
+            const double cost = double(npb) * (mf + stage + late + (nbuf == 2 ? 400.0 : 900.0));
             if (!found || cost < best) {
                 found = true;
                 best = cost;

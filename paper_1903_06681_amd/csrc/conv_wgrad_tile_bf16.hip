@@ -5,7 +5,7 @@ namespace dc {
 
 hipError_t launch_wgrad_tile_bf16(const WgradArgs& a, hipStream_t s) {
 #define X(id, now, ncw, wo, wc, wt, wk, tw) \
-    if (a.tcfg == id) return launch_wgrad_tile<1, now, ncw, wo, wc, wt, wk, tw, 128, 1>(a, s);
+    if (a.tcfg == id) return launch_wgrad_tile<1, now, ncw, wo, wc, wt, wk, tw, wt_pixels(1, id), 1>(a, s);
     DC_WT_CONFIGS(X)
 #undef X
     return hipErrorInvalidValue;

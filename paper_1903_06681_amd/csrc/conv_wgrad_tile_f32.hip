@@ -6,7 +6,7 @@ namespace dc {
 hipError_t launch_wgrad_tile_f32(const WgradArgs& a, hipStream_t s) {
 #define X(id, now, ncw, wo, wc, wt, wk, tw) \
     if constexpr (id <= 5 || id == 7) { \
-        if (a.tcfg == id) return launch_wgrad_tile<3, now, ncw, wo, wc, wt, wk, tw, 64, 1>(a, s); \
+        if (a.tcfg == id) return launch_wgrad_tile<3, now, ncw, wo, wc, wt, wk, tw, wt_pixels(3, id), 1>(a, s); \
     }
     DC_WT_CONFIGS(X)
 #undef X
