@@ -104,13 +104,18 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
 }
 
 // dw = (accumulate ? dw : 0) + the sum of the chunks' partials: chunk group g
-// (of 4) adds chunks g, g + 4, ... in order, then groups 0..3.  A workgroup
-// takes 256 consecutive floats of the partials, a quarter of one 32 x 32
-// block, so that the block's place is scalar arithmetic and each thread moves
-// four filters' values with 16-byte loads.  Bound: HBM (the partials).
-__global__ __launch_bounds__(256) void wgrad_tile_reduce_kernel(WgradArgs a) {
+// (of G) adds chunks g, g + G, ... in order, then groups 0 .. G - 1.  A
+// workgroup takes 256 consecutive floats of the partials, a quarter of one
+// 32 x 32 block, so that the block's place is scalar arithmetic and each
+// thread moves four filters' values with 16-byte loads.  Bound: HBM (the
+// partials); where the quarters leave CUs idle the round trips of one thread,
+// hence sixteen groups from 32 chunks on (us: 256 chunks of 40 quarters, fp32
+// 32 -> 32 stride 2 on a 512x512 tile, 8.9 with four groups, 6.7 with sixteen;
+// 64 chunks of 640 quarters 8.4 and 11.7).
+template <int G>
+__global__ __launch_bounds__(64 * G) void wgrad_tile_reduce_kernel(WgradArgs a) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    __shared__ f32x4 red[4][64];
+    __shared__ f32x4 red[G][64];
     const int q = blockIdx.x & 3, blk = blockIdx.x >> 2, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int nbw = a.ttw * a.tnow * a.tncw;
     const int b = blk % nbw, w = blk / nbw, wsub = w % a.tnws, zz = w / a.tnws;
@@ -125,18 +130,20 @@ __global__ __launch_bounds__(256) void wgrad_tile_reduce_kernel(WgradArgs a) {
     const int64_t step = a.F / 4;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
     int c = g;
-    for (; c + 12 < a.nchunks; c += 16) {   // four loads in flight, added in chunk order
+    for (; c + 3 * G < a.nchunks; c += 4 * G) {   // four loads in flight, added in chunk order
         f32x4 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = src[(c + 4 * j) * step];
+        for (int j = 0; j < 4; ++j) v[j] = src[(c + G * j) * step];
 #pragma unroll
         for (int j = 0; j < 4; ++j) sum += v[j];
     }
-    for (; c < a.nchunks; c += 4) sum += src[c * step];
+    for (; c < a.nchunks; c += G) sum += src[c * step];
     red[g][lane] = sum;
     __syncthreads();
     if (g != 0) return;
-    const f32x4 total = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    f32x4 total = red[0][lane];
+#pragma unroll
+    for (int k = 1; k < G; ++k) total += red[k][lane];
     const int o = o0 + 4 * (lane >> 5), ci = c0 + (lane & 31);
     if (ci >= a.C) return;
 #pragma unroll
@@ -150,7 +157,9 @@ __global__ __launch_bounds__(256) void wgrad_tile_reduce_kernel(WgradArgs a) {
 hipError_t launch_wgrad_tile(const WgradArgs& a, int dtype, hipStream_t s) {
     hipError_t e = dtype == 1 ? launch_wgrad_tile_bf16(a, s) : launch_wgrad_tile_f32(a, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(wgrad_tile_reduce_kernel, dim3(unsigned(a.F / 256)), dim3(256), 0, s, a);
+    const dim3 grid(unsigned(a.F / 256));
+    if (a.nchunks >= 32 && a.F <= 65536) hipLaunchKernelGGL(wgrad_tile_reduce_kernel<16>, grid, dim3(64 * 16), 0, s, a);
+    else hipLaunchKernelGGL(wgrad_tile_reduce_kernel<4>, grid, dim3(64 * 4), 0, s, a);
     return hipGetLastError();
 }
 
