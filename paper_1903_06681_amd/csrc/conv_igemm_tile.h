@@ -53,6 +53,7 @@ static constexpr int kTileWord3 = 0x00020000;   // buffer resource word 3 (gfx9 
 // plan keeps those below 2^31): such a load returns 0, such a store is dropped.
 static constexpr uint32_t kTileOut = 0x80000000u;
 static constexpr int kTileNT = 2;               // a buffer store's non-temporal bit
+static constexpr int kTileRedoBytes = 16;       // fp32: LDS of the redo word, past the records
 
 // weight staging: per-element gathers (any layout); forward, a thread's 8
 // channels x T taps as T 16-byte loads; backward-data, 8 x 8 blocks
@@ -209,6 +210,11 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             v[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rin, off + j * pstep, 0, 0));
     };
     PartRange range;
+    // the word that says so to the whole workgroup, past the staged records (a
+    // static __shared__ word or __syncthreads_or() would come on top of plans that
+    // allot the whole LDS); the chunk loop's barriers part this store from any other
+    uint32_t* redo = reinterpret_cast<uint32_t*>(smem + a.lds_bytes - kTileRedoBytes);
+    if (NS == 3 && threadIdx.x == 0) *redo = 0;
     auto store_patch = [&](const uint4 (&v)[8], int slot, int lim) __attribute__((always_inline)) {
         if (slot < 0) return;
         const int step = PSU, odd = de ? (ROW / 2) * PSU : 0;
@@ -478,7 +484,9 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
     float* out = a.out + tile * a.out_tile + int64_t(n) * a.Cout * oplane;
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.Cout * oplane * 4, kTileWord3);
     if constexpr (NS == 3) {
-        if (__syncthreads_or(int(range.outside()))) {
+        if (range.outside()) *redo = 1;
+        __syncthreads();
+        if (*redo) {
             const float* inf = reinterpret_cast<const float*>(in);
             const float* wf = static_cast<const float*>(a.w);
             for (int e = threadIdx.x; e < OB * np * NPH; e += kTileThreads * KG) {

@@ -32,6 +32,7 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
         else if (a.wmode == 1 && int64_t(a.Cout) * T % 8 == 0) wm = kWBlocks;
         if (wm != kWRows && a.Cin <= 16) ccg = 2;
     }
+    const int extra = NS == 3 ? kTileRedoBytes : 0;
     const int limit = device_lds_limit(), cus = device_cu_count();
     static const Cfg plain_bf16[] = {{0, 64, 256, 2, 2}, {1, 64, 128, 2, 1}, {2, 64, 64, 1, 1}, {3, 32, 256, 1, 2}, {4, 128, 128, 2, 2}};
     static const Cfg plain_f32[] = {{1, 64, 128, 2, 1}, {2, 64, 64, 1, 1}, {3, 32, 256, 1, 2}, {5, 32, 128, 1, 1}};
@@ -80,7 +81,7 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
             const int pr = (bu - 1) * a.istr + a.Tr;
             const int64_t grec = int64_t(NS) * T * tile_trec(ccg, f.OB) + int64_t(pr) * pg * GW * tile_psu(NS, ccg);
             const int64_t sums = kg == 2 ? int64_t(a.bp ? 4 : 1) * f.NOBW * f.NPBW * 4 * 4096 : 0;
-            const int64_t lds = std::max(grec * 16 * kg, sums);
+            const int64_t lds = std::max(grec * 16 * kg, sums) + extra;
             if (lds > limit) continue;
             const int occ = lds * 2 <= limit ? 2 : 1;
             const int64_t npb = images * nub * nvb;

@@ -47,6 +47,7 @@ namespace dc {
 static constexpr int kWtThreads = 512;
 static constexpr int kWtWord3 = 0x00020000;          // buffer resource word 3 (gfx9 family: raw access)
 static constexpr uint32_t kWtOut = 0x80000000u;      // byte offset past every buffer here: loads 0
+static constexpr int kWtRedoBytes = 16;              // fp32: LDS of the redo word, past everything else
 
 template <int NS, int NOW, int NCW, int WO, int WC, int WT, int WK, int TW, int P, int UPT>
 __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) {
@@ -297,6 +298,11 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
         }
     };
 
+    // fp32: the word that says to the whole workgroup that the parts do not hold a
+    // value, past the staged records and the sums (a static __shared__ word or
+    // __syncthreads_or() would come on top of plans that allot the whole LDS)
+    u32* redo_word = reinterpret_cast<u32*>(smem + a.lds_bytes - kWtRedoBytes);
+    if (NS == 3 && tid == 0) *redo_word = 0;
     // dy records past the block's pixels are never staged: zero them once (and the
     // zero record) in every buffer
     for (int e = tid; e < a.tnbuf * NS * NOB * DPIX * 4; e += kWtThreads) {
@@ -326,7 +332,11 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
         }
     }
     bool redo = false;
-    if constexpr (NS == 3) redo = __syncthreads_or(int(range.outside()));
+    if constexpr (NS == 3) {
+        if (range.outside()) *redo_word = 1;
+        __syncthreads();
+        redo = *redo_word;
+    }
 
     // ---- the wave groups' sums, added pairwise in LDS in a fixed order
     constexpr int NBW = TW * NOW * NCW, NWS = WO * WC * WT;

@@ -34,7 +34,8 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
     const Cfg& f = kCfgs[id];
     const int P = wt_pixels(NS, id);
     const int OBK = 32 * f.now * f.wo, CBK = 32 * f.ncw * f.wc, NOB = OBK / 32, NCB = CBK / 32;
-    const int limit = device_lds_limit();
+    const int extra = NS == 3 ? kWtRedoBytes : 0;
+    const int limit = device_lds_limit() - extra;
     const int nws = f.wo * f.wc * f.wt, nbw = f.tw * f.now * f.ncw;
     const int64_t red = f.wk > 1 ? int64_t(f.wk / 2) * nws * nbw * 4096 : 0;
     if (red > limit) return false;
@@ -70,7 +71,7 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
                 best = cost;
                 t->tbu = bu; t->tbv = bv; t->tnub = nub; t->nqb = nvb; t->tpg = pg; t->tdg = dg;
                 t->tnpb = int(npb); t->tnbuf = nbuf;
-                t->lds_bytes = int(std::max(lds * nbuf, red));
+                t->lds_bytes = int(std::max(lds * nbuf, red)) + extra;
             }
         }
     }

@@ -43,6 +43,8 @@ LAYERS = [
     # 1x1, 5x5, 7x7
     _layer("bf16", 2, 72, 200, 13, 17, 1), _layer("bf16", 1, 281, 48, 9, 35, 1), _layer("f32", 2, 72, 40, 13, 17, 1),
     _layer("bf16", 1, 40, 24, 30, 30, 5), _layer("f32", 1, 20, 40, 20, 30, 5), _layer("bf16", 1, 64, 9, 20, 28, 7),
+    # fp32 plans that take a workgroup's whole LDS, or 16 bytes less than would not fit
+    _layer("f32", 1, 72, 72, 57, 3, 3, 2), _layer("f32", 1, 40, 72, 61, 4, 4), _layer("f32", 1, 16, 72, 66, 6, 4, 2),
 ]
 
 

@@ -5,6 +5,7 @@ brute-force index sets (Sec. III-A)."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -260,3 +261,23 @@ def test_tiles_beyond_32bit_indexing_validate_single_samples_must_fit():
     assert dc.bwd_filter_workspace_bytes(big, 0) > 0
     huge = prob(N=1, C=2048, K=64, H=1024, W=1024, P=1, Q=1, dtype=dc.DC_BF16)
     assert dc.validate(huge, 0) == -11                   # one sample alone is too large
+
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.mark.skipif(not os.path.exists(f"{LLVM}/clang-offload-bundler"), reason="ROCm toolchain missing")
+@pytest.mark.parametrize("unit", ["conv_igemm_tile_bf16", "conv_igemm_tile_bp", "conv_igemm_tile_f32",
+                                  "conv_wgrad_tile_bf16", "conv_wgrad_tile_f32"])
+def test_blocked_kernels_hold_no_static_lds(unit, tmp_path):
+    """The blocked plans allot up to the whole LDS of a workgroup dynamically: a
+    static word on top would ask for more than there is, and the launch would fail."""
+    obj = os.path.join(ROOT, "paper_1903_06681_amd", "_build", unit + ".hip.o")
+    fat, dev = str(tmp_path / "fat.bin"), str(tmp_path / "dev.o")
+    subprocess.run([f"{LLVM}/llvm-objcopy", "--dump-section", f".hip_fatbin={fat}", obj, str(tmp_path / "copy.o")],
+                   check=True)
+    subprocess.run([f"{LLVM}/clang-offload-bundler", "--unbundle", "--type=o", f"--input={fat}", f"--output={dev}",
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+    notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", dev], capture_output=True, text=True, check=True).stdout
+    lds = [int(v) for v in re.findall(r"\.group_segment_fixed_size:\s*(\d+)", notes)]
+    assert lds and set(lds) == {0}, lds
