@@ -153,19 +153,22 @@ __device__ __forceinline__ int div16(int e, uint32_t m) { return m ? int(__umulh
 
 // What the three bf16 parts of a value cannot hold exactly: infinities, NaN,
 // magnitudes from 2^62 (their part products could overflow where the fp32
-// product does not) and nonzero ones below 2^-117 (the last part would lie
-// below bf16's range).  Tracked on the leading parts, two values a word:
-// `hi` their largest magnitudes, `lo` the smallest minus one (so that zero is
-// the largest).
+// product does not) and nonzero ones below 2^-110 (a value's last bit lies 23
+// binades below its first, bf16's last subnormal is 2^-133).  `hi` keeps the
+// largest magnitudes of the leading parts, two values a word; `lo` the
+// smallest of the values themselves, without the sign and minus one (so that
+// zero is the largest): a leading part says nothing there, values below 2^-134
+// round to a zero one.
 struct PartRange {
     uint32_t hi = 0, lo = 0xffffffffu;
     __device__ __forceinline__ bool outside() const {
-        return (hi & 0xffffu) >= 0x5e80u || (hi >> 16) >= 0x5e80u || (lo & 0xffffu) < 0x04ffu || (lo >> 16) < 0x04ffu;
+        return (hi & 0xffffu) >= 0x5e80u || (hi >> 16) >= 0x5e80u || lo < (0x08800000u << 1) - 1;
     }
 };
 
 // 8 fp32 values -> three records of bf16 parts (round to nearest, remainder,
-// again): each part holds 8 bits and a sign, so three hold all 24
+// again): each part holds 8 bits and a sign, so three hold all 24 of a value
+// within PartRange
 __device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], PartRange& range) {
     typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
     typedef float f2 __attribute__((ext_vector_type(2)));
@@ -174,6 +177,7 @@ __device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], PartR
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float a = f[2 * i], b = f[2 * i + 1];
+        range.lo = min(range.lo, min((__builtin_bit_cast(uint32_t, a) << 1) - 1, (__builtin_bit_cast(uint32_t, b) << 1) - 1));
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
             const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf2));
@@ -185,8 +189,6 @@ __device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], PartR
         }
         const us2 m = __builtin_bit_cast(us2, w[0][i] & 0x7fff7fffu);
         range.hi = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, range.hi), m));
-        range.lo = __builtin_bit_cast(
-            uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, range.lo), us2(m - us2{1, 1})));
     }
 #pragma unroll
     for (int s = 0; s < 3; ++s) p[s] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};

@@ -114,3 +114,54 @@ def test_fp32_extremes(L):
             # scaling by a power of two is exact but for inputs below 2^-126
             e = np.max(np.abs(g.astype(np.float64) / (sx * sw) - clean)) / np.max(np.abs(clean))
             assert e <= (1e-5 if sx > 2.0 ** -100 else 2e-5), (name, sx, e)
+
+
+# layers whose three passes all run on the blocked kernels (weight gradient: more than 256 outputs)
+BOTTOM = [_layer("f32", 1, 40, 72, 24, 24, 3), _layer("f32", 1, 36, 48, 33, 30, 3, 2), _layer("f32", 2, 64, 96, 12, 20, 1)]
+
+
+def _rel(g, r):
+    return float(np.linalg.norm(g.astype(np.float64) - r) / np.linalg.norm(r))
+
+
+@pytest.mark.parametrize("L", BOTTOM, ids=_id)
+@pytest.mark.parametrize("lo,hi", [(-117, -115), (-126, -117), (-149, -134)])
+@pytest.mark.parametrize("tiny", ["x", "w", "dy"])
+def test_fp32_bottom_of_the_range(L, lo, hi, tiny):
+    """One tensor between 2^lo and 2^hi (from the last bits that three bf16 parts hold
+    down to fp32's last subnormals), the other two near 2^60: normal-sized results.
+
+    Limit: up to 648 products are added in 32 bits, whose roundings (each at most
+    2^-24 of a partial sum, of random sign) come to sqrt(648 / 3) * 2^-24 = 9e-7 of
+    the result if every partial sum were as large as the last; 1e-6."""
+    print(f"[bottom] {_id(L)} {tiny} 2^{lo}..2^{hi}", flush=True)
+    rng = np.random.default_rng(L.seed + lo)
+    t = {}
+    for name in ("x", "w", "dy"):
+        a = wl.draw(L, name)
+        if name == tiny:
+            a = np.ldexp(np.sign(a) * (1 + rng.random(a.shape)), rng.integers(lo, hi, a.shape)).astype(np.float32)
+            assert np.all(a != 0)
+        else:
+            a = np.ldexp(a, 60)
+        t[name] = a
+    for name, got, ref in zip(("y", "dx", "dw"), _run(L, **t), _oracle(L, **t)):
+        assert np.all(np.isfinite(got)) and _rel(got, ref) <= 1e-6, (name, _rel(got, ref))
+
+
+@pytest.mark.parametrize("L", BOTTOM, ids=_id)
+@pytest.mark.parametrize("value", [2.0 ** -112 * 1.2345678, 2.0 ** -140])
+def test_fp32_one_tiny_value(L, value):
+    """A single tiny value in x and in dy, alone in the windows that read it: the outputs
+    that read it get it whole (one product, rounded once), all others keep fp32's accuracy."""
+    print(f"[tiny] {_id(L)} {value}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    w = np.ldexp(w, 40)
+    x[:, :, 4:11, 6:13], dy[:, :, 3:10, 2:9] = 0, 0
+    x[0, 5, 7, 9], dy[0, 7, 6, 5] = value, value
+    got, ref = _run(L, x, w, dy), _oracle(L, x, w, dy)
+    for name, g, r in zip(("y", "dx", "dw"), got, ref):
+        assert np.all(np.isfinite(g)) and _rel(g, r) <= 1e-6, (name, _rel(g, r))
+        if name != "dw":
+            one = (r != 0) & (np.abs(r) < 2.0 ** -60)
+            assert one.any() and np.max(np.abs(g[one] - r[one]) / np.abs(r[one])) <= 2.0 ** -23, name
