@@ -155,20 +155,22 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
 
     // ---- staging units of this thread
     uint32_t poff[UPT];            // patch: byte offset for channel group 0 of a chunk
-    int pslot[UPT], plim[UPT];     // LDS record of pixel 0 (-1: none), columns left in the padded row
+    int pslot[UPT], pcol[UPT];     // LDS record of pixel 0 (-1: none), its column in the padded row
     const uint32_t pstep = uint32_t(plane) * ES;   // bytes per channel
-    auto patch_unit = [&](int e, uint32_t& off, int& slot, int& lim) __attribute__((always_inline)) {
+    auto patch_unit = [&](int e, uint32_t& off, int& slot, int& col) __attribute__((always_inline)) {
         const int cg = e % CCG, rest = e / CCG;
         const int pr = div16(rest, a.tmpg), g = rest - pr * PG;
         const int gr = row0 + pr, gc = ca + g * GW;
-        const bool in_lds = pr < PR, ok = in_lds & (gr < a.in_rows) & (gc < a.in_pitch);
+        const bool in_lds = pr < PR;
+        const bool ok = in_lds & (NS == 1 ? (gr < a.in_rows) & (gc < a.in_pitch)
+                                          : (gr >= a.sr0) & (gr < a.sr1) & (gc + GW > a.sc0) & (gc < a.sc1));
         off = ok ? uint32_t(gr * a.in_pitch + gc) * ES + cg * 8 * pstep : kTileOut;
         slot = in_lds ? (pr * ROW + (de ? g * (GW / 2) : g * GW)) * PSU + cg : -1;
-        lim = a.in_cols - gc;
+        col = gc;
     };
     const int npu = PR * PG * CCG;
 #pragma unroll
-    for (int q = 0; q < UPT; ++q) patch_unit(tid + q * kTileThreads, poff[q], pslot[q], plim[q]);
+    for (int q = 0; q < UPT; ++q) patch_unit(tid + q * kTileThreads, poff[q], pslot[q], pcol[q]);
 
     // weight units: kWGather (tap, group, o) with taps fastest; kWRows (o,
     // group); kWBlocks (group, 8 consecutive (o, tap))
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
     // allot the whole LDS); the chunk loop's barriers part this store from any other
     uint32_t* redo = reinterpret_cast<uint32_t*>(smem + a.lds_bytes - kTileRedoBytes);
     if (NS == 3 && threadIdx.x == 0) *redo = 0;
-    auto store_patch = [&](const uint4 (&v)[8], int slot, int lim) __attribute__((always_inline)) {
+    auto store_patch = [&](const uint4 (&v)[8], int slot, int col) __attribute__((always_inline)) {
         if (slot < 0) return;
         const int step = PSU, odd = de ? (ROW / 2) * PSU : 0;
         if constexpr (NS == 1) {
@@ -239,11 +241,11 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
                 f[j][0] = __builtin_bit_cast(float, v[j].x); f[j][1] = __builtin_bit_cast(float, v[j].y);
                 f[j][2] = __builtin_bit_cast(float, v[j].z); f[j][3] = __builtin_bit_cast(float, v[j].w);
             }
-            // columns of the pitch hold anything and feed no stored pixel
-            if (lim < GW) {
+            // columns that feed no stored pixel (the pitch, margins beside an interior) hold anything
+            if (col < a.sc0 || col + GW > a.sc1) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (i >= lim)
+                    if (col + i < a.sc0 || col + i >= a.sc1)
 #pragma unroll
                         for (int j = 0; j < 8; ++j) f[j][i] = 0.f;
             }
@@ -355,7 +357,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q]);
         }
 #pragma unroll
-        for (int q = 0; q < UPT; ++q) store_patch(xs[q], pslot[q], plim[q]);
+        for (int q = 0; q < UPT; ++q) store_patch(xs[q], pslot[q], pcol[q]);
         // units beyond the registers' share
         for (int e = tid + WPT * kTileThreads; e < nwu; e += kTileThreads) {
             uint32_t off;
@@ -373,11 +375,11 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         }
         for (int e = tid + UPT * kTileThreads; e < npu; e += kTileThreads) {
             uint32_t off;
-            int slot, lim;
-            patch_unit(e, off, slot, lim);
+            int slot, col;
+            patch_unit(e, off, slot, col);
             uint4 v[8];
             load_patch(v, off, c0);
-            store_patch(v, slot, lim);
+            store_patch(v, slot, col);
         }
     };
 

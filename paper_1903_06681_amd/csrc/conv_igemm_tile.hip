@@ -113,6 +113,10 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
     }
     if (!found) return false;
     a.twm = wm; a.tccg = ccg;
+    a.sr0 = std::max(a.base_r, a.own);
+    a.sr1 = std::min(a.base_r + (a.Uo - 1) * a.istr + a.Tr, a.in_rows - a.own);
+    a.sc0 = std::max(a.base_c, a.own);
+    a.sc1 = std::min(a.base_c + (a.Vo - 1) * a.istr + a.Ts, a.in_cols - a.own);
     auto magic = [](int d) { return d > 1 ? uint32_t((uint64_t(1) << 32) / uint32_t(d) + 1) : 0u; };
     a.tmt = magic(T); a.tmpg = magic(a.tpg); a.tmbv = magic(a.tbv); a.tmnf = magic(a.OB * T / 8);
     a.kind = 5;

@@ -77,6 +77,9 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
     const int buf_bytes = (NS * (NOB * DPIX + NCB * XPIX)) * 64;
     const int XO = NS * NOB * DPIX * 64;
     const int shx = a.base_c % GW, shd = a.dy_off % GW;
+    // x rows and columns up to here are read by the sums; fp32: what lies outside is
+    // staged as zero, as the contents of a cell may choose the arithmetic of its chunk
+    const int xr1 = a.base_r + (a.Hot - 1) * st + a.R, xc1 = a.base_c + (a.Wot - 1) * st + a.S;
 
     // ---- staging units: dy first (rounded up to whole waves), then x
     const int ndu = (a.tbu * DG * (OBK / 8) + 63) & ~63;
@@ -129,7 +132,8 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
             const_cast<char*>(base), 0, int(step) * (isd ? a.K : a.C), kWtWord3);
         const int row = u.row + (isd ? k.u0 : a.base_r + k.u0 * st);
         const int col = u.col + (isd ? a.dy_off + k.v0 : k.v0 * st);
-        const bool ok = (row < (isd ? a.Hot : a.x_rows)) & (col < (isd ? a.dy_pitch : a.x_pitch));
+        const int rows = isd ? a.Hot : NS == 1 ? a.x_rows : xr1, cols = isd ? a.dy_pitch : NS == 1 ? a.x_pitch : xc1;
+        const bool ok = (row < rows) & (col < cols);
         const u32 at = u.off + (isd ? u32(k.u0 * a.dy_pitch + k.v0) : u32((k.u0 * a.x_pitch + k.v0) * st)) * ES;
         const u32 off = ok ? at : kWtOut;
 #pragma unroll
@@ -176,13 +180,17 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
                 const bool in = (vl >= 0) & (vl < a.tbv);
                 put(i, (in ? row + vl : P) * 4, in & (i < end));
             }
-        } else if (a.x_cols - k.v0 * st - u.col >= GW) {
+        } else {
+            // the row's first and last vectors: the pitch, and in fp32 what no sum reads, hold anything
+            const int col = u.col + k.v0 * st, c0 = NS == 1 ? 0 : a.base_c, c1 = NS == 1 ? a.x_cols : xc1;
+            if (col >= c0 && col + GW <= c1) {
 #pragma unroll
-            for (int i = 0; i < GW; ++i) put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, true);
-        } else {   // the row's last vector: the pitch holds anything
+                for (int i = 0; i < GW; ++i) put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, true);
+            } else {
 #pragma unroll
-            for (int i = 0; i < GW; ++i)
-                put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, i < a.x_cols - k.v0 * st - u.col);
+                for (int i = 0; i < GW; ++i)
+                    put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, (col + i >= c0) & (col + i < c1));
+            }
         }
     };
     const int nu = ndu + nxu;

@@ -424,6 +424,7 @@ dc_status dc_conv_fwd_region(const dc_problem* prob, int32_t tile, int32_t regio
     // stride 1: the outputs that read x's halo bands are the frame of those
     // widths (output row p reads input rows p - pad .. p - pad + R - 1)
     if (region == DC_REGION_BOUNDARY) igemm_set_frame(a, g.bw_x);
+    if (region == DC_REGION_INTERIOR) a.own = g.h;
     std::vector<IgemmArgs> launches;
     if (!plan_groups(g, a, g.x_sample, g.y_sample, launches)) return DC_ERR_UNSUPPORTED;
     return launch_all(launches, g.dtype, static_cast<hipStream_t>(stream));
@@ -526,6 +527,7 @@ dc_status dc_conv_bwd_data_region(const dc_problem* prob, int32_t tile, int32_t 
             // stride 1: the inputs whose gradient reads dy's halo bands are the
             // frame of those widths (dx row i reads dy rows i + pad - R + 1 .. i + pad)
             if (region == DC_REGION_BOUNDARY) igemm_set_frame(a, g.bw_dy);
+            if (region == DC_REGION_INTERIOR) a.own = g.h;
             if (!plan_groups(g, a, g.dy_sample, g.dx_sample, phases)) return DC_ERR_UNSUPPORTED;
         }
     }

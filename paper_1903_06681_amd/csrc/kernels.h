@@ -93,6 +93,11 @@ struct IgemmArgs {
     // (tnub block rows x nvb block columns per image, tnpb in all), 16-byte
     // vectors per patch row
     int tcfg, tccg, twm, tnob, tnpb, tbu, tbv, tnub, tpg;
+    // rows [sr0, sr1) and columns [sc0, sc1) of the padded input that stored
+    // outputs read, fp32: what lies outside is staged as zero, as the contents
+    // of a cell may choose the arithmetic of its block
+    int sr0, sr1, sc0, sc1;
+    int own;                     // interior launch: width of the margins, which no stored output reads
     int tkg, tgrec;              // groups of waves that share the channel chunks (1 or 2), their LDS records
     int nt;                      // outputs leave by non-temporal stores (blocked, rolling-row kernels)
     uint32_t tmt, tmpg, tmbv, tmnf;   // 2^32 / d + 1 of the kernel's divisors (0 for 1)

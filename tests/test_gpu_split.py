@@ -171,3 +171,47 @@ def test_overlapped_split_schedule_equals_serial(name):
         xt3, dyt3 = xt2.clone(), dyt2.clone()   # margins NaN again
         y2, dx2 = _split(L, p, xt3, dyt3, wd, sa, sb)
         assert torch.equal(_bits(y1), _bits(y2)) and torch.equal(_bits(dx1), _bits(dx2))
+
+
+@pytest.mark.parametrize("L", [
+    # fp32 layers whose interior runs on the blocked kernel: both passes, one 64-wide
+    # block a row and several, a margin wider than the padding, a channel remainder
+    Layer("m1", 1, 40, 72, 32, 48, 3, 3, 1, 1, 2, 2, 1, "f32", "uniform", 220),
+    Layer("m2", 1, 24, 32, 60, 288, 3, 3, 1, 1, 2, 2, 3, "f32", "uniform", 221),
+    Layer("m3", 2, 20, 33, 26, 38, 5, 5, 1, 2, 2, 2, 2, "f32", "uniform", 222),
+    wl.small("c4", H=96, W=80, P=3, Q=2),
+], ids=lambda L: f"{L.C}-{L.K}-k{L.R}h{L.halo}")
+def test_margins_do_not_reach_interior_bits(L):
+    """The interior may run while the margins are being written: whatever they hold
+    (NaN, infinities, subnormals, zeros, the neighbours' values), outputs outside the
+    frame have the same bits, those of the whole-tile pass."""
+    p, x, w, dy, xt, dyt, wd = _setup(L)
+    nt, h = L.P * L.Q, L.halo
+    shapes = ((nt, L.N, L.K, L.Hot, L.Wot), (nt, L.N, L.C, L.Ht, L.Wt))
+    rng = torch.Generator(device="cuda").manual_seed(7)
+
+    def interior(region):
+        y, dx = (torch.zeros(s, device="cuda") for s in shapes)
+        dc.conv_fwd_region(p, ALL, region, xt, wd, y)
+        dc.conv_bwd_data_region(p, ALL, region, dyt, wd, dx)
+        torch.cuda.synchronize()
+        out = []
+        for o, bw in ((y, dc.halo_bands(p, X)), (dx, dc.halo_bands(p, DY))):
+            out.append(_bits(o)[..., bw[0]:o.shape[-2] - bw[1], bw[2]:o.shape[-1] - bw[3]].clone())
+        return out
+
+    def fill(values):
+        for t, th, tw in ((xt, L.Ht, L.Wt), (dyt, L.Hot, L.Wot)):
+            block = t[..., h:h + th, h:h + tw].clone()
+            t.copy_(values[torch.randint(len(values), t.shape, generator=rng, device="cuda")])
+            t[..., h:h + th, h:h + tw] = block
+
+    H.fill_halos_all_tiles(p, X, xt, L.dtype)
+    H.fill_halos_all_tiles(p, DY, dyt, L.dtype)
+    want = interior(dc.DC_REGION_ALL)
+    seen = {"neighbours": interior(INT)}
+    for name, values in (("nan", [float("nan")]), ("zero", [0.0]), ("stale", [1e-40, -2.0 ** -112, 3e38, float("inf"), 0.5])):
+        fill(torch.tensor(values, device="cuda"))
+        seen[name] = interior(INT)
+    for name, got in seen.items():
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), name
