@@ -151,33 +151,32 @@ __device__ __forceinline__ uint4 mask8(uint4 v, int nv) {
 // e / d for e, d < 2^16 by the host's m = 2^32 / d + 1 (0 for d = 1)
 __device__ __forceinline__ int div16(int e, uint32_t m) { return m ? int(__umulhi(uint32_t(e), m)) : e; }
 
-// What the three bf16 parts of a value cannot hold exactly: infinities, NaN,
-// magnitudes from 2^62 (their part products could overflow where the fp32
-// product does not) and nonzero ones below 2^-110 (a value's last bit lies 23
-// binades below its first, bf16's last subnormal is 2^-133).  `hi` keeps the
-// largest magnitudes of the leading parts, two values a word; `lo` the
-// smallest of the values themselves, without the sign and minus one (so that
-// zero is the largest): a leading part says nothing there, values below 2^-134
-// round to a zero one.
+// The smallest of the staged values, without the sign and minus one (so that
+// zero is the largest).  Nonzero values below 2^-110 do not fit three bf16
+// parts: a value's last bit lies 23 binades below its first, bf16's last
+// subnormal is 2^-133.  (The leading part would not tell: below 2^-134 it
+// rounds to zero.)  Too large values need no such watch: parts and part
+// products that overflow, like infinities and NaN, leave infinities or NaN in
+// every sum that they reach.
 struct PartRange {
-    uint32_t hi = 0, lo = 0xffffffffu;
-    __device__ __forceinline__ bool outside() const {
-        return (hi & 0xffffu) >= 0x5e80u || (hi >> 16) >= 0x5e80u || lo < (0x08800000u << 1) - 1;
-    }
+    static constexpr uint32_t kLeast = 0x08800000u << 1;   // 2^-110
+    uint32_t lo = 0xffffffffu;
+    __device__ static __forceinline__ uint32_t key(uint32_t u) { return (u << 1) - 1; }
+    __device__ static __forceinline__ bool tiny(uint32_t u) { return key(u) < kLeast - 1; }
+    __device__ __forceinline__ bool outside() const { return lo < kLeast - 1; }
 };
 
 // 8 fp32 values -> three records of bf16 parts (round to nearest, remainder,
 // again): each part holds 8 bits and a sign, so three hold all 24 of a value
-// within PartRange
+// that is not tiny
 __device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], PartRange& range) {
     typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
     typedef float f2 __attribute__((ext_vector_type(2)));
-    typedef uint16_t us2 __attribute__((ext_vector_type(2)));
     uint32_t w[3][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float a = f[2 * i], b = f[2 * i + 1];
-        range.lo = min(range.lo, min((__builtin_bit_cast(uint32_t, a) << 1) - 1, (__builtin_bit_cast(uint32_t, b) << 1) - 1));
+        range.lo = min(range.lo, min(PartRange::key(__builtin_bit_cast(uint32_t, a)), PartRange::key(__builtin_bit_cast(uint32_t, b))));
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
             const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), bf2));
@@ -187,8 +186,6 @@ __device__ __forceinline__ void split8(const float (&f)[8], uint4 (&p)[3], PartR
             }
             w[s][i] = u;
         }
-        const us2 m = __builtin_bit_cast(us2, w[0][i] & 0x7fff7fffu);
-        range.hi = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, range.hi), m));
     }
 #pragma unroll
     for (int s = 0; s < 3; ++s) p[s] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};

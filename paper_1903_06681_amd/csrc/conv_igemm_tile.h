@@ -27,9 +27,10 @@
 // bits), and the product is formed from the six part products of weight above
 // 2^-24 (parts 0*0, 0*1, 1*0, 1*1, 0*2, 2*0); what is left out is about 2^-26
 // of a product and of random sign.  Six bf16 MFMAs take 16 channels in 192
-// cycles; v_mfma_f32_32x32x2_f32 takes 512.  Values the parts cannot hold
-// (infinities, NaN, magnitudes near the ends of the range) are noticed while
-// staging, and the workgroup then computes its block in plain fp32.
+// cycles; v_mfma_f32_32x32x2_f32 takes 512.  A block that meets values the
+// parts cannot hold (infinities, NaN, magnitudes near the ends of the range)
+// is computed once more on the fp32 instruction, from the same staging, for
+// the outputs that read them.
 //
 // Bound: the matrix cores at many channels; what holds it is staging (waits
 // for loads and barriers, 2 waves per SIMD).  Measured against the chunked
@@ -71,28 +72,6 @@ __device__ __forceinline__ uint32_t pair16(const uint32_t (&d)[N], int e0, int e
     const uint32_t lo = d[e0 >> 1], hi = d[e1 >> 1];
     const uint32_t sel = ((e0 & 1) ? 0x0302u : 0x0100u) | ((e1 & 1) ? 0x07060000u : 0x05040000u);
     return __builtin_amdgcn_perm(hi, lo, sel);
-}
-
-// One output element in plain fp32, straight from the tensors: the path of
-// blocks whose values the bf16 parts cannot hold.
-__device__ inline float tile_direct(const IgemmArgs& a, const float* in, const float* w, int o, int u, int v,
-                                    int ph) {
-    const int py = ph >> 1, px = ph & 1;
-    const int ntr = a.bp ? a.bptr[py] : a.Tr, nts = a.bp ? a.bpts[px] : a.Ts;
-    const int dr = a.bp ? a.bpdr[py] : 0, dc_ = a.bp ? a.bpdc[px] : 0;
-    const int r0 = a.bp ? a.bpr0[py] : a.wr0, rs = a.bp ? -2 : a.wrstep;
-    const int s0 = a.bp ? a.bps0[px] : a.ws0, ss = a.bp ? -2 : a.wsstep;
-    const int64_t plane = int64_t(a.in_rows) * a.in_pitch;
-    float sum = 0.f;
-    for (int ci = 0; ci < a.Cin; ++ci)
-        for (int tr = 0; tr < ntr; ++tr)
-            for (int ts = 0; ts < nts; ++ts) {
-                const int gr = u * a.istr + a.base_r + dr + tr, gc = v * a.istr + a.base_c + dc_ + ts;
-                if (gr < 0 || gr >= a.in_rows || gc < 0 || gc >= a.in_cols) continue;
-                sum = fmaf(w[o * a.w_os + ci * a.w_cs + (r0 + rs * tr) * a.S + s0 + ss * ts],
-                           in[ci * plane + int64_t(gr) * a.in_pitch + gc], sum);
-            }
-    return sum;
 }
 
 hipError_t launch_tile_bf16(const IgemmArgs& a, hipStream_t s);
@@ -212,12 +191,32 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             v[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rin, off + j * pstep, 0, 0));
     };
     PartRange range;
-    // the word that says so to the whole workgroup, past the staged records (a
-    // static __shared__ word or __syncthreads_or() would come on top of plans that
-    // allot the whole LDS); the chunk loop's barriers part this store from any other
+    // fp32: the word that says to the whole workgroup that the parts do not hold a
+    // value, past the staged records (a static __shared__ word or __syncthreads_or()
+    // would come on top of plans that allot the whole LDS); the chunk loop's barriers
+    // part this store from any other
     uint32_t* redo = reinterpret_cast<uint32_t*>(smem + a.lds_bytes - kTileRedoBytes);
     if (NS == 3 && threadIdx.x == 0) *redo = 0;
-    auto store_patch = [&](const uint4 (&v)[8], int slot, int col) __attribute__((always_inline)) {
+    // Plain fp32 (rawc): the eight channels of a record as fp32 words in its first two
+    // parts; the third part's first word marks the patch pixels and the output channels
+    // that hold a value the parts do not.
+    auto patch_mark = [&](int pixel) __attribute__((always_inline)) {
+        return reinterpret_cast<uint32_t*>(pl + pixel * PSU + 2 * CCG);
+    };
+    auto weight_mark = [&](int o) __attribute__((always_inline)) { return reinterpret_cast<uint32_t*>(wl + 2 * WPL + o); };
+    auto put_raw = [](const float (&f)[8], uint4& r0, uint4& r1) __attribute__((always_inline)) {
+        uint32_t w[8];
+        bool tiny = false;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            w[j] = __builtin_bit_cast(uint32_t, f[j]);
+            tiny |= PartRange::tiny(w[j]);
+        }
+        r0 = uint4{w[0], w[1], w[2], w[3]};
+        r1 = uint4{w[4], w[5], w[6], w[7]};
+        return tiny;
+    };
+    auto store_patch = [&](auto rawc, const uint4 (&v)[8], int slot, int col) __attribute__((always_inline)) {
         if (slot < 0) return;
         const int step = PSU, odd = de ? (ROW / 2) * PSU : 0;
         if constexpr (NS == 1) {
@@ -252,11 +251,15 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float g[8] = {f[0][i], f[1][i], f[2][i], f[3][i], f[4][i], f[5][i], f[6][i], f[7][i]};
-                uint4 p[3];
-                split8(g, p, range);
                 const int at = slot + (de ? (i / 2) * step + (i & 1) * odd : i * step);
+                if constexpr (decltype(rawc)::value) {
+                    if (put_raw(g, pl[at], pl[at + CCG])) *patch_mark(at / PSU) = 1;
+                } else {
+                    uint4 p[3];
+                    split8(g, p, range);
 #pragma unroll
-                for (int s = 0; s < 3; ++s) pl[at + s * CCG] = p[s];
+                    for (int s = 0; s < 3; ++s) pl[at + s * CCG] = p[s];
+                }
             }
         }
     };
@@ -286,7 +289,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             else v[j] = __builtin_amdgcn_raw_buffer_load_b32(rw, b, 0, 0);
         }
     };
-    auto store_g = [&](const u32 (&v)[8], int slot) __attribute__((always_inline)) {
+    auto store_g = [&](auto rawc, const u32 (&v)[8], int slot) __attribute__((always_inline)) {
         if (slot < 0) return;
         if constexpr (NS == 1) {
             uint4 r;
@@ -297,10 +300,14 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             float f[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = __builtin_bit_cast(float, v[j]);
-            uint4 p[3];
-            split8(f, p, range);
+            if constexpr (decltype(rawc)::value) {
+                if (put_raw(f, wl[slot], wl[slot + WPL])) *weight_mark(slot % TREC % GREC) = 1;
+            } else {
+                uint4 p[3];
+                split8(f, p, range);
 #pragma unroll
-            for (int s = 0; s < 3; ++s) wl[s * WPL + slot] = p[s];
+                for (int s = 0; s < 3; ++s) wl[s * WPL + slot] = p[s];
+            }
         }
     };
     auto store_w = [&](const uint4 (&v)[WV], int slot, int cg) __attribute__((always_inline)) {
@@ -348,50 +355,45 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
 #pragma unroll
         for (int q = 0; q < UPT; ++q) load_patch(xs[q], poff[q], c0);
     };
-    auto store_chunk = [&](int c0) __attribute__((always_inline)) {
-        if constexpr (WM == kWGather) {
+    auto store_chunk = [&](auto rawc, int c0) __attribute__((always_inline)) {
+        constexpr bool RAW = decltype(rawc)::value;   // holds nothing in registers
+        if constexpr (!RAW) {
+            if constexpr (WM == kWGather) {
 #pragma unroll
-            for (int q = 0; q < WPT; ++q) store_g(gs[q], wslot[q]);
-        } else {
+                for (int q = 0; q < WPT; ++q) store_g(rawc, gs[q], wslot[q]);
+            } else {
 #pragma unroll
-            for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q]);
+                for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < UPT; ++q) store_patch(rawc, xs[q], pslot[q], pcol[q]);
         }
-#pragma unroll
-        for (int q = 0; q < UPT; ++q) store_patch(xs[q], pslot[q], pcol[q]);
         // units beyond the registers' share
-        for (int e = tid + WPT * kTileThreads; e < nwu; e += kTileThreads) {
+        for (int e = tid + (RAW ? 0 : WPT) * kTileThreads; e < nwu; e += kTileThreads) {
             uint32_t off;
             int slot, cg;
             w_unit(e, off, slot, cg);
             if constexpr (WM == kWGather) {
                 u32 v[8];
                 load_g(v, off, cg, c0);
-                store_g(v, slot);
+                store_g(rawc, v, slot);
             } else {
                 uint4 v[WV];
                 load_w(v, off, cg, c0);
                 store_w(v, slot, cg);
             }
         }
-        for (int e = tid + UPT * kTileThreads; e < npu; e += kTileThreads) {
+        for (int e = tid + (RAW ? 0 : UPT) * kTileThreads; e < npu; e += kTileThreads) {
             uint32_t off;
             int slot, col;
             patch_unit(e, off, slot, col);
             uint4 v[8];
             load_patch(v, off, c0);
-            store_patch(v, slot, col);
+            store_patch(rawc, v, slot, col);
         }
     };
 
     floatx16 acc[NPH][NOBW][NPBW];
-#pragma unroll
-    for (int ph = 0; ph < NPH; ++ph)
-#pragma unroll
-        for (int i = 0; i < NOBW; ++i)
-#pragma unroll
-            for (int j = 0; j < NPBW; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[ph][i][j][e] = 0.f;
 
     // this lane's pixels (past the block's last: a repeat of it, never stored)
     const int np = bu * bv;
@@ -408,128 +410,141 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         return (tr * ROW + (de ? (c >> 1) + (c & 1) * (ROW / 2) : c)) * PSU;
     };
     // one k-step: records ar of the weights, br of the patch (per lane half)
-    auto kstep = [&](int ar, int br, bool zero, floatx16 (&c)[NOBW][NPBW]) __attribute__((always_inline)) {
-        bf16x8 A[NS][NOBW], B[NS][NPBW];
+    auto kstep = [&](auto rawc, int ar, int br, bool zero, floatx16 (&c)[NOBW][NPBW]) __attribute__((always_inline)) {
+        constexpr int NR = decltype(rawc)::value ? 2 : NS;
+        uint4 A[NR][NOBW], B[NR][NPBW];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
+        for (int s = 0; s < NR; ++s) {
 #pragma unroll
             for (int i = 0; i < NOBW; ++i) {
-                uint4 r = wl[s * WPL + ar + abase + i * 32];
-                if (zero) r = uint4{0, 0, 0, 0};
-                A[s][i] = __builtin_bit_cast(bf16x8, r);
+                A[s][i] = wl[s * WPL + ar + abase + i * 32];
+                if (zero) A[s][i] = uint4{0, 0, 0, 0};
             }
 #pragma unroll
             for (int j = 0; j < NPBW; ++j) {
-                uint4 r = pl[br + pix[j] + s * CCG];
-                if (zero) r = uint4{0, 0, 0, 0};
-                B[s][j] = __builtin_bit_cast(bf16x8, r);
+                B[s][j] = pl[br + pix[j] + s * CCG];
+                if (zero) B[s][j] = uint4{0, 0, 0, 0};
             }
         }
-        constexpr int NP = NS == 1 ? 1 : 6;
-        constexpr int pa[6] = {0, 2, 1, 1, 0, 0}, pb[6] = {2, 0, 1, 0, 1, 0};   // small products first
+        if constexpr (decltype(rawc)::value) {
+            // two channels an instruction, one of each half's group
+            static_for<0, 8>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int k = decltype(kc)::value;
+                auto word = [](const uint4& r) __attribute__((always_inline)) {
+                    return __builtin_bit_cast(float, k % 4 == 0 ? r.x : k % 4 == 1 ? r.y : k % 4 == 2 ? r.z : r.w);
+                };
 #pragma unroll
-        for (int k = 0; k < NP; ++k)
+                for (int i = 0; i < NOBW; ++i)
 #pragma unroll
-            for (int i = 0; i < NOBW; ++i)
+                    for (int j = 0; j < NPBW; ++j)
+                        c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(word(A[k / 4][i]), word(B[k / 4][j]), c[i][j], 0, 0, 0);
+            });
+        } else {
+            constexpr int NP = NS == 1 ? 1 : 6;
+            constexpr int pa[6] = {0, 2, 1, 1, 0, 0}, pb[6] = {2, 0, 1, 0, 1, 0};   // small products first
 #pragma unroll
-                for (int j = 0; j < NPBW; ++j)
-                    c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[NS == 1 ? 0 : pa[k]][i],
-                                                                      B[NS == 1 ? 0 : pb[k]][j], c[i][j], 0, 0, 0);
+            for (int k = 0; k < NP; ++k)
+#pragma unroll
+                for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                    for (int j = 0; j < NPBW; ++j)
+                        c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8, A[NS == 1 ? 0 : pa[k]][i]),
+                            __builtin_bit_cast(bf16x8, B[NS == 1 ? 0 : pb[k]][j]), c[i][j], 0, 0, 0);
+        }
     };
 
     const int cin = a.Tr > 0 ? a.Cin : 0;   // an output phase without taps is zero
     constexpr int STEP = KG * CC;
-    if (kg * CC < cin) load_chunk(kg * CC);
-    for (int c1 = 0; c1 < cin; c1 += STEP) {
-        const int c0 = c1 + kg * CC;
-        const bool mine = KG == 1 || c0 < cin;
-        if (c1 > 0) __syncthreads();
-        if (mine) store_chunk(c0);
-        __syncthreads();
-        if (c0 + STEP < cin) load_chunk(c0 + STEP);
-        if (!mine) continue;
-        const int ng = min(CCG, (a.Cin - c0 + 7) / 8);   // channel groups of this chunk
+    // the whole reduction: all channel chunks into acc
+    auto sweep = [&](auto rawc) __attribute__((always_inline)) {
 #pragma unroll
-        for (int ph = 0; ph < NPH; ++ph) {
-            const int py = ph >> 1, px = ph & 1;
-            const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
-            const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
-            const int r0 = BP ? a.bpr0[py] : a.wr0, rs = BP ? -2 : a.wrstep;
-            const int s0 = BP ? a.bps0[px] : a.ws0, ss = BP ? -2 : a.wsstep;
-            for (int tr = 0; tr < ntr; ++tr)
-                for (int ts = 0; ts < nts; ++ts) {
-                    const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
+        for (int ph = 0; ph < NPH; ++ph)
 #pragma unroll
-                    for (int g = 0; g + 1 < CCG; g += 2)
-                        if (g + 1 < ng) kstep(ao + (g + hi) * GREC, bo + g + hi, false, acc[ph]);
-                }
-            if (ng & 1) {
-                // a last lone group: two taps per k-step, one per half of the lanes
-                const int g = ng - 1, nt = ntr * nts;
-                int tr1 = 0, ts1 = 0;
-                for (int i = 0; i < nt; i += 2) {
-                    int tr2 = tr1, ts2 = ts1;
-                    if (i + 1 < nt && ++ts2 == nts) { ts2 = 0; ++tr2; }
-                    const int tr = hi ? tr2 : tr1, ts = hi ? ts2 : ts1;
-                    const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
-                    kstep(ao + g * GREC, bo + g, (i + 1 >= nt) & hi, acc[ph]);
-                    tr1 = tr2; ts1 = ts2;
-                    if (++ts1 == nts) { ts1 = 0; ++tr1; }
+            for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                for (int j = 0; j < NPBW; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[ph][i][j][e] = 0.f;
+        constexpr bool AHEAD = !decltype(rawc)::value;
+        if (AHEAD && kg * CC < cin) load_chunk(kg * CC);
+        for (int c1 = 0; c1 < cin; c1 += STEP) {
+            const int c0 = c1 + kg * CC;
+            const bool mine = KG == 1 || c0 < cin;
+            if (c1 > 0) __syncthreads();
+            if (mine) store_chunk(rawc, c0);
+            __syncthreads();
+            if (AHEAD && c0 + STEP < cin) load_chunk(c0 + STEP);
+            if (!mine) continue;
+            const int ng = min(CCG, (a.Cin - c0 + 7) / 8);   // channel groups of this chunk
+#pragma unroll
+            for (int ph = 0; ph < NPH; ++ph) {
+                const int py = ph >> 1, px = ph & 1;
+                const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
+                const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
+                const int r0 = BP ? a.bpr0[py] : a.wr0, rs = BP ? -2 : a.wrstep;
+                const int s0 = BP ? a.bps0[px] : a.ws0, ss = BP ? -2 : a.wsstep;
+                for (int tr = 0; tr < ntr; ++tr)
+                    for (int ts = 0; ts < nts; ++ts) {
+                        const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
+#pragma unroll
+                        for (int g = 0; g + 1 < CCG; g += 2)
+                            if (g + 1 < ng) kstep(rawc, ao + (g + hi) * GREC, bo + g + hi, false, acc[ph]);
+                    }
+                if (ng & 1) {
+                    // a last lone group: two taps per k-step, one per half of the lanes
+                    const int g = ng - 1, nt = ntr * nts;
+                    int tr1 = 0, ts1 = 0;
+                    for (int i = 0; i < nt; i += 2) {
+                        int tr2 = tr1, ts2 = ts1;
+                        if (i + 1 < nt && ++ts2 == nts) { ts2 = 0; ++tr2; }
+                        const int tr = hi ? tr2 : tr1, ts = hi ? ts2 : ts1;
+                        const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
+                        kstep(rawc, ao + g * GREC, bo + g, (i + 1 >= nt) & hi, acc[ph]);
+                        tr1 = tr2; ts1 = ts2;
+                        if (++ts1 == nts) { ts1 = 0; ++tr1; }
+                    }
                 }
             }
         }
-    }
+    };
+    // group 1's sums to LDS, added by group 0
+    auto join = [&]() __attribute__((always_inline)) {
+        if constexpr (KG > 1) {
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
+            constexpr int NT = NPH * NOBW * NPBW;
+            f32x4* red = reinterpret_cast<f32x4*>(smem) + wave * NT * 256 + lane;
+            __syncthreads();
+            if (kg == 1) {
+                static_for<0, NT>([&](auto tc) __attribute__((always_inline)) {
+                    constexpr int t = decltype(tc)::value;
+                    const floatx16& v = acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) red[(t * 4 + q) * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+                });
+            }
+            __syncthreads();
+            if (kg == 1) return;
+            static_for<0, NT>([&](auto tc) __attribute__((always_inline)) {
+                constexpr int t = decltype(tc)::value;
+                floatx16& v = acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 f = red[(t * 4 + q) * 64];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[4 * q + j] += f[j];
+                }
+            });
+        }
+    };
+    sweep(std::false_type{});
+    join();
 
     // D of a 32x32 tile: value e of lane l is row 8*(e/4) + 4*(l/32) + e%4
     // (output channel), column l%32 (pixel)
     const int oplane = a.out_rows * a.out_cols;
     float* out = a.out + tile * a.out_tile + int64_t(n) * a.Cout * oplane;
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.Cout * oplane * 4, kTileWord3);
-    if constexpr (NS == 3) {
-        if (range.outside()) *redo = 1;
-        __syncthreads();
-        if (*redo) {
-            const float* inf = reinterpret_cast<const float*>(in);
-            const float* wf = static_cast<const float*>(a.w);
-            for (int e = threadIdx.x; e < OB * np * NPH; e += kTileThreads * KG) {
-                const int p = e % np, rest = e / np;
-                const int ph = rest % NPH, o = o0 + rest / NPH;
-                const int ul = p / bv, u = u0 + ul, v = v0 + p - ul * bv;
-                if (v >= a.Vo) continue;
-                const int orow = u * a.ostr + (BP ? ph >> 1 : a.oph_r), ocol = v * a.ostr + (BP ? ph & 1 : a.oph_c);
-                if (o >= a.Cout || orow >= a.out_rows || ocol >= a.out_cols) continue;
-                out[int64_t(o) * oplane + int64_t(orow) * a.out_cols + ocol] = tile_direct(a, inf, wf, o, u, v, ph);
-            }
-            return;
-        }
-    }
-    if constexpr (KG > 1) {
-        // group 1's sums to LDS, added by group 0
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        constexpr int NT = NPH * NOBW * NPBW;
-        f32x4* red = reinterpret_cast<f32x4*>(smem) + wave * NT * 256 + lane;
-        __syncthreads();
-        if (kg == 1) {
-            static_for<0, NT>([&](auto tc) __attribute__((always_inline)) {
-                constexpr int t = decltype(tc)::value;
-                const floatx16& v = acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) red[(t * 4 + q) * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-            });
-        }
-        __syncthreads();
-        if (kg == 1) return;
-        static_for<0, NT>([&](auto tc) __attribute__((always_inline)) {
-            constexpr int t = decltype(tc)::value;
-            floatx16& v = acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 f = red[(t * 4 + q) * 64];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[4 * q + j] += f[j];
-            }
-        });
-    }
     auto finish = [&](auto ntc) __attribute__((always_inline)) {
     constexpr int AUX = decltype(ntc)::value;
 #pragma unroll
@@ -570,8 +585,80 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         }
     }
     };
-    if (a.nt) finish(std::integral_constant<int, kTileNT>{});
-    else finish(std::integral_constant<int, 0>{});
+    if (kg == 0) {
+        if (a.nt) finish(std::integral_constant<int, kTileNT>{});
+        else finish(std::integral_constant<int, 0>{});
+    }
+    if constexpr (NS == 3) {
+        // Values the parts cannot hold: below 2^-110 noticed while staging, and too large
+        // ones, infinities and NaN by what they leave in a sum.  The block is then swept
+        // once more in plain fp32, and the outputs that such a value reaches, no others,
+        // are replaced: an output's bits depend on its own window and weights only.  The
+        // fp32 instruction and staging without loads ahead take two to four times the
+        // first sweep (128 -> 128 3x3 on a 64x64 tile: 31 us plain, 68 with one such value
+        // a tensor, 101 with nothing else; a scalar loop per output took 1,490).
+        float odd = 0.f;   // NaN where a sum is not finite
+        static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) odd = fmaf(acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW][e], 0.f, odd);
+        });
+        if (range.outside() || (kg == 0 && !(odd == 0.f))) *redo = 1;
+        __syncthreads();
+        if (!*redo) return;
+        uint32_t bad[NPH][NOBW][NPBW];
+        static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(tc)::value;
+            uint32_t& b = bad[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
+            b = 0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                b |= isfinite(acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW][e]) ? 0u : 1u << e;
+        });
+        __threadfence();   // the stores above come before those below
+        for (int e = tid; e < PR * ROW; e += kTileThreads) *patch_mark(e) = 0;
+        for (int e = tid; e < OB; e += kTileThreads) *weight_mark(e) = 0;
+        __syncthreads();
+        sweep(std::true_type{});
+        __syncthreads();
+        for (int k = 0; k < KG; ++k) {   // the groups' marks
+            const uint4* wk = reinterpret_cast<uint4*>(smem) + k * a.tgrec;
+            const uint4* pk = wk + NS * T * TREC;
+            uint32_t rows[NOBW];
+#pragma unroll
+            for (int i = 0; i < NOBW; ++i) {
+                rows[i] = 0;
+                for (int e = 0; e < 16; ++e)
+                    rows[i] |= wk[2 * WPL + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4].x ? 1u << e : 0u;
+            }
+            static_for<0, NPH * NPBW>([&](auto tc) __attribute__((always_inline)) {
+                constexpr int ph = decltype(tc)::value / NPBW, j = decltype(tc)::value % NPBW;
+                const int py = ph >> 1, px = ph & 1;
+                const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
+                const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
+                uint32_t mark = 0;
+                for (int tr = 0; tr < ntr; ++tr)
+                    for (int ts = 0; ts < nts; ++ts) mark |= pk[tap_b(dr + tr, dcol + ts) + pix[j] + 2 * CCG].x;
+#pragma unroll
+                for (int i = 0; i < NOBW; ++i) bad[ph][i][j] |= mark ? 0xffffu : rows[i];
+            });
+        }
+        join();
+        if (kg != 0) return;
+        static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
+            constexpr int ph = decltype(tc)::value / (NOBW * NPBW), i = decltype(tc)::value / NPBW % NOBW, j = decltype(tc)::value % NPBW;
+            const int p = (wp * NPBW + j) * 32 + l32;
+            const int ul = div16(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
+            const int orow = u * a.ostr + (BP ? ph >> 1 : a.oph_r), ocol = v * a.ostr + (BP ? ph & 1 : a.oph_c);
+            if (p >= np || v >= a.Vo || orow >= a.out_rows || ocol >= a.out_cols) return;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int o = o0 + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4;
+                if ((bad[ph][i][j] >> e & 1) && o < a.Cout)
+                    out[int64_t(o) * oplane + int64_t(orow) * a.out_cols + ocol] = acc[ph][i][j][e];
+            }
+        });
+    }
 }
 
 template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG = 1>

@@ -27,7 +27,7 @@
 //
 // fp32 layers use three bf16 parts per value and six part products, as the
 // blocked convolution does (conv_igemm_tile.h); chunks whose values the parts
-// cannot hold are redone in plain fp32.
+// cannot hold are swept once more on the fp32 instruction.
 //
 // Bound: staging (two channels of 16-byte loads, transposes and LDS writes per
 // block) and one barrier a block; matrix work is about a quarter.  Measured
@@ -141,7 +141,8 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
             v[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + j * step, 0, 0));
     };
     PartRange range;
-    auto store_unit = [&](const uint4 (&v)[8], const Unit& u, int e, const Block& k, unsigned char* buf)
+    // rawc: plain fp32, the eight channels of a record as fp32 words in its first two parts
+    auto store_unit = [&](auto rawc, const uint4 (&v)[8], const Unit& u, int e, const Block& k, unsigned char* buf)
         __attribute__((always_inline)) {
         if (u.row >= 1 << 20) return;
         const bool isd = __builtin_amdgcn_readfirstlane(e) < ndu;
@@ -164,10 +165,15 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
                 float f[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) f[j] = live ? __builtin_bit_cast(float, word(j, i)) : 0.f;
-                uint4 p[3];
-                split8(f, p, range);
+                if constexpr (decltype(rawc)::value) {
+                    l[at] = __builtin_bit_cast(uint4, f32x4{f[0], f[1], f[2], f[3]});
+                    l[at + splane] = __builtin_bit_cast(uint4, f32x4{f[4], f[5], f[6], f[7]});
+                } else {
+                    uint4 p[3];
+                    split8(f, p, range);
 #pragma unroll
-                for (int s = 0; s < 3; ++s) l[at + s * splane] = p[s];
+                    for (int s = 0; s < 3; ++s) l[at + s * splane] = p[s];
+                }
             }
         };
         if (isd) {
@@ -199,15 +205,18 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
 #pragma unroll
         for (int q = 0; q < UPT; ++q) load_unit(xs[q], un[q], tid + q * kWtThreads, k);
     };
-    auto store_block = [&](const Block& k, unsigned char* buf) __attribute__((always_inline)) {
+    auto store_block = [&](auto rawc, const Block& k, unsigned char* buf) __attribute__((always_inline)) {
+        constexpr bool RAW = decltype(rawc)::value;   // holds nothing in registers
+        if constexpr (!RAW) {
 #pragma unroll
-        for (int q = 0; q < UPT; ++q) store_unit(xs[q], un[q], tid + q * kWtThreads, k, buf);
-        for (int e = tid + UPT * kWtThreads; e < ((nu + 63) & ~63); e += kWtThreads) {
+            for (int q = 0; q < UPT; ++q) store_unit(rawc, xs[q], un[q], tid + q * kWtThreads, k, buf);
+        }
+        for (int e = tid + (RAW ? 0 : UPT) * kWtThreads; e < ((nu + 63) & ~63); e += kWtThreads) {
             Unit u;
             make_unit(e, u);
             uint4 v[8];
             load_unit(v, u, e, k);
-            store_unit(v, u, e, k, buf);
+            store_unit(rawc, v, u, e, k, buf);
         }
     };
 
@@ -231,18 +240,9 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
         toff[i] = (r * ROW + (de ? (c >> 1) + (c & 1) * (ROW / 2) : c)) * 64;
     }
     floatx16 acc[TW][NOW][NCW];
-#pragma unroll
-    for (int i = 0; i < TW; ++i)
-#pragma unroll
-        for (int o = 0; o < NOW; ++o)
-#pragma unroll
-            for (int c = 0; c < NCW; ++c)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][o][c][e] = 0.f;
 
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) s16x4* lds4;
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
     const u32 lds0 = u32(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem));
     auto frag = [&](u32 p0, u32 p1) __attribute__((always_inline)) {
         const s16x4 f0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(uintptr_t)p0);
@@ -306,75 +306,136 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
         }
     };
 
+    // the same sums on the fp32 instruction, two pixels each: a lane's half takes pixels
+    // 8 (l/32) .. + 7 of a k-step, its filter and channel are l%32 of their blocks
+    auto compute_raw = [&](unsigned char* buf, int bu, int bv) __attribute__((always_inline)) {
+        const int np = bu * a.tbv, l32 = lane & 31;
+        const int word = (l32 / 8) * 16 + (l32 & 3) * 4, part = (l32 >> 2) & 1;
+        auto at = [&](int off) __attribute__((always_inline)) { return *reinterpret_cast<const float*>(buf + off + word); };
+        for (int k = wk * 16; k < np; k += WK * 16)
+            for (int m = 0; m < 8; ++m) {
+                const int p = k + 8 * (lane >> 5) + m, ul = div16(p, a.tmbv), vl = p - ul * a.tbv;
+                const bool in = (p < np) & (vl < bv);
+                const int px = (ul * st * ROW + (de ? vl : vl * st)) * 64;
+                float A[NOW];
+#pragma unroll
+                for (int o = 0; o < NOW; ++o) A[o] = at(((part * NOB + wo * NOW + o) * DPIX + p) * 64);
+                static_for<0, TW>([&](auto ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(ic)::value;
+#pragma unroll
+                    for (int c = 0; c < NCW; ++c) {
+                        const float B = at(in ? XO + (part * NCB + wc * NCW + c) * XPIX * 64 + px + toff[i] : (DPIX - 1) * 64);
+#pragma unroll
+                        for (int o = 0; o < NOW; ++o)
+                            acc[i][o][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[o], B, acc[i][o][c], 0, 0, 0);
+                    }
+                });
+            }
+    };
+
     // fp32: the word that says to the whole workgroup that the parts do not hold a
     // value, past the staged records and the sums (a static __shared__ word or
     // __syncthreads_or() would come on top of plans that allot the whole LDS)
     u32* redo_word = reinterpret_cast<u32*>(smem + a.lds_bytes - kWtRedoBytes);
     if (NS == 3 && tid == 0) *redo_word = 0;
-    // dy records past the block's pixels are never staged: zero them once (and the
-    // zero record) in every buffer
-    for (int e = tid; e < a.tnbuf * NS * NOB * DPIX * 4; e += kWtThreads) {
-        const int per_buf = NS * NOB * DPIX * 4, b = e / per_buf, f = e - b * per_buf;
-        *(reinterpret_cast<uint4*>(smem + b * buf_bytes) + f) = uint4{0, 0, 0, 0};
-    }
-    if (b0 < b1) {
-        Block cur = block(b0);
-        load_block(cur);
-        __syncthreads();
-        store_block(cur, smem);
-        Block nxt = b0 + 1 < b1 ? block(b0 + 1) : cur;
-        if (b0 + 1 < b1) load_block(nxt);
-        __syncthreads();
-        for (int b = b0; b < b1; ++b) {
-            const int cb = a.tnbuf == 2 ? (b - b0) & 1 : 0;
-            compute(lds0 + cb * buf_bytes, min(a.tbu, a.Hot - cur.u0), min(a.tbv, a.Wot - cur.v0));
-            if (b + 1 == b1) break;
-            if (a.tnbuf == 1) __syncthreads();
-            store_block(nxt, smem + (a.tnbuf == 2 ? (cb ^ 1) * buf_bytes : 0));
-            cur = nxt;
-            if (b + 2 < b1) {
-                nxt = block(b + 2);
-                load_block(nxt);
-            }
-            __syncthreads();
+    // all pixel blocks of the chunk into acc
+    auto sweep = [&](auto rawc) __attribute__((always_inline)) {
+        constexpr bool RAW = decltype(rawc)::value;
+        static_for<0, TW * NOW * NCW>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW][e] = 0.f;
+        });
+        // dy records past the block's pixels are never staged: zero them once (and the
+        // zero record) in every buffer
+        for (int e = tid; e < a.tnbuf * NS * NOB * DPIX * 4; e += kWtThreads) {
+            const int per_buf = NS * NOB * DPIX * 4, b = e / per_buf, f = e - b * per_buf;
+            *(reinterpret_cast<uint4*>(smem + b * buf_bytes) + f) = uint4{0, 0, 0, 0};
         }
-    }
-    bool redo = false;
-    if constexpr (NS == 3) {
-        if (range.outside()) *redo_word = 1;
-        __syncthreads();
-        redo = *redo_word;
-    }
+        if (b0 >= b1) return;
+        if constexpr (RAW) {
+            for (int b = b0; b < b1; ++b) {
+                const Block k = block(b);
+                __syncthreads();
+                store_block(rawc, k, smem);
+                __syncthreads();
+                compute_raw(smem, min(a.tbu, a.Hot - k.u0), min(a.tbv, a.Wot - k.v0));
+            }
+        } else {
+            Block cur = block(b0);
+            load_block(cur);
+            __syncthreads();
+            store_block(rawc, cur, smem);
+            Block nxt = b0 + 1 < b1 ? block(b0 + 1) : cur;
+            if (b0 + 1 < b1) load_block(nxt);
+            __syncthreads();
+            for (int b = b0; b < b1; ++b) {
+                const int cb = a.tnbuf == 2 ? (b - b0) & 1 : 0;
+                compute(lds0 + cb * buf_bytes, min(a.tbu, a.Hot - cur.u0), min(a.tbv, a.Wot - cur.v0));
+                if (b + 1 == b1) break;
+                if (a.tnbuf == 1) __syncthreads();
+                store_block(rawc, nxt, smem + (a.tnbuf == 2 ? (cb ^ 1) * buf_bytes : 0));
+                cur = nxt;
+                if (b + 2 < b1) {
+                    nxt = block(b + 2);
+                    load_block(nxt);
+                }
+                __syncthreads();
+            }
+        }
+    };
 
     // ---- the wave groups' sums, added pairwise in LDS in a fixed order
     constexpr int NBW = TW * NOW * NCW, NWS = WO * WC * WT;
     f32x4* red = reinterpret_cast<f32x4*>(smem);
+    auto join = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int half = WK / 2; half >= 1; half /= 2) {
-        __syncthreads();
-        if (wk >= half && wk < 2 * half) {
-            f32x4* d = red + (((wk - half) * NWS + wsub) * NBW) * 256 + lane;
-            static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
-                constexpr int i = decltype(ic)::value;
-                const floatx16& v = acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW];
+        for (int half = WK / 2; half >= 1; half /= 2) {
+            __syncthreads();
+            if (wk >= half && wk < 2 * half) {
+                f32x4* d = red + (((wk - half) * NWS + wsub) * NBW) * 256 + lane;
+                static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(ic)::value;
+                    const floatx16& v = acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    d[(i * 4 + q) * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-            });
+                    for (int q = 0; q < 4; ++q)
+                        d[(i * 4 + q) * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+                });
+            }
+            __syncthreads();
+            if (wk < half) {
+                const f32x4* d = red + ((wk * NWS + wsub) * NBW) * 256 + lane;
+                static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(ic)::value;
+                    floatx16& v = acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 f = d[(i * 4 + q) * 64];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) v[4 * q + j] += f[j];
+                    }
+                });
+            }
         }
+    };
+    sweep(std::false_type{});
+    join();
+    if constexpr (NS == 3) {
+        // Values the parts cannot hold: below 2^-110 noticed while staging, and too large
+        // ones, infinities and NaN by what they leave in a sum.  The chunk is then swept
+        // once more on the fp32 instruction (128 -> 128 3x3 on a 64x64 tile: 30 us plain, 44
+        // with one such value, 49 with nothing else; a scalar loop per sum took 1,110).
+        float odd = 0.f;   // NaN where a sum is not finite
+        static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) odd = fmaf(acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW][e], 0.f, odd);
+        });
+        if (range.outside() || (wk == 0 && !(odd == 0.f))) *redo_word = 1;
         __syncthreads();
-        if (wk < half) {
-            const f32x4* d = red + ((wk * NWS + wsub) * NBW) * 256 + lane;
-            static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
-                constexpr int i = decltype(ic)::value;
-                floatx16& v = acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 f = d[(i * 4 + q) * 64];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[4 * q + j] += f[j];
-                }
-            });
+        if (*redo_word) {
+            sweep(std::true_type{});
+            join();
         }
     }
     // partial: [chunk][gy][gz][wave][tap][o block][c block][4][64 lanes][4]; value j of
@@ -382,30 +443,6 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
     if (wk > 0) return;
     float* part = a.part + int64_t(blockIdx.x) * a.F +
                   ((int64_t(blockIdx.y) * a.gz + blockIdx.z) * NWS + wsub) * NBW * 1024;
-    if (NS == 3 && redo) {
-        // plain fp32, a value at a time
-        for (int i = 0; i < NBW * 16; ++i) {
-            const int blk = i / 16, q = i / 4 % 4, j = i % 4;
-            const int t = tap0 + blk / (NOW * NCW);
-            const int o = o0 + (wo * NOW + blk / NCW % NOW) * 32 + 8 * q + 4 * (lane >> 5) + j;
-            const int ci = c0 + (wc * NCW + blk % NCW) * 32 + (lane & 31);
-            float sum = 0.f;
-            if (t < T && o < a.K && ci < a.C) {
-                const int r = t / a.S, s = t - r * a.S;
-                for (int b = b0; b < b1; ++b) {
-                    const Block k = block(b);
-                    const float* x = reinterpret_cast<const float*>(k.x) + int64_t(ci) * xplane;
-                    const float* dy = reinterpret_cast<const float*>(k.dy) + int64_t(o) * dplane;
-                    for (int u = k.u0; u < min(k.u0 + a.tbu, a.Hot); ++u)
-                        for (int v = k.v0; v < min(k.v0 + a.tbv, a.Wot); ++v)
-                            sum = fmaf(dy[(a.dy_off + u) * a.dy_pitch + a.dy_off + v],
-                                       x[(u * st + a.base_r + r) * a.x_pitch + v * st + a.base_c + s], sum);
-                }
-            }
-            part[blk * 1024 + (q * 64 + lane) * 4 + j] = sum;
-        }
-        return;
-    }
     static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
         if (tap0 + i / (NOW * NCW) >= T) return;

@@ -165,3 +165,62 @@ def test_fp32_one_tiny_value(L, value):
         if name != "dw":
             one = (r != 0) & (np.abs(r) < 2.0 ** -60)
             assert one.any() and np.max(np.abs(g[one] - r[one]) / np.abs(r[one])) <= 2.0 ** -23, name
+
+
+def _reads(L, at, out):
+    """The outputs (mask over H x W of y, or of dx) whose window holds input pixel `at`."""
+    one = np.zeros((1, 1) + ((L.H, L.W) if out == "y" else (L.Ho, L.Wo)), np.float32)
+    one[(0, 0) + at] = 1
+    k = np.ones((1, 1, L.R, L.S), np.float32)
+    f = orc.conv_fwd(one, k, L.stride, L.pad) if out == "y" else orc.conv_bwd_data(one, k, L.H, L.W, L.stride, L.pad)
+    return f[0, 0] != 0
+
+
+@pytest.mark.parametrize("L", BOTTOM + [_layer("f32", 1, 72, 72, 57, 3, 3, 2), _layer("f32", 1, 128, 128, 40, 44, 3)], ids=_id)
+@pytest.mark.parametrize("value", [1e-40, 2.0 ** -112, 3e38, np.inf, np.nan])
+def test_fp32_fallback_replaces_only_the_outputs_that_read_the_value(L, value):
+    """Values that three bf16 parts do not hold change the arithmetic of the outputs that
+    read them; every other output keeps its bits."""
+    print(f"[fallback] {_id(L)} {value}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    w = w * np.float32(0.1)
+    clean = _run(L, x, w, dy)
+    xat, dat = (7, 1), (5, 1)
+    xv, dyv = x.copy(), dy.copy()
+    xv[0, 3][xat], dyv[0, 9][dat] = value, value
+    got = _run(L, xv, w, dyv)
+    t = [torch.from_numpy(a).double() for a in (xv, w, dyv)]
+    ref = (torch.nn.functional.conv2d(t[0], t[1], stride=L.stride, padding=L.pad).numpy(),
+           torch.nn.grad.conv2d_input(t[0].shape, t[1], t[2], L.stride, L.pad).numpy())
+    for name, g, c, r, at in (("y", got[0], clean[0], ref[0], xat), ("dx", got[1], clean[1], ref[1], dat)):
+        m = _reads(L, at, name)
+        assert m.any() and not m.all()
+        assert np.array_equal(g[:, :, ~m], c[:, :, ~m]), name
+        if L.N > 1:
+            assert np.array_equal(g[1:], c[1:]), name
+        g, r = g[0][:, m], r[0][:, m]
+        fin = np.isfinite(r) & (np.abs(r) < 3e38)
+        assert np.array_equal(np.isnan(g), np.isnan(r)) and np.array_equal(g[np.isinf(r)], r[np.isinf(r)].astype(np.float32))
+        if fin.any():
+            assert np.max(np.abs(g[fin] - r[fin])) <= 1e-5 * np.max(np.abs(r[fin])), name
+
+
+@pytest.mark.parametrize("L", BOTTOM + [_layer("f32", 2, 20, 24, 26, 38, 5), _layer("f32", 1, 34, 40, 30, 70, 7),
+                                        _layer("f32", 1, 24, 24, 26, 39, 3, P=2, Q=3, halo=3)], ids=_id)
+@pytest.mark.parametrize("value", [1e-40, 2.0 ** -112, 3e38, np.inf, np.nan])
+def test_fp32_weight_gradient_with_values_the_parts_do_not_hold(L, value):
+    """The chunk that holds such a value is added in plain fp32: finite results keep
+    fp32's accuracy, infinities and NaN appear where the sums have them."""
+    print(f"[dw fallback] {_id(L)} {value}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    x[0, 3, 7, 2], dy[0, 9, 5, 1], dy[0, 9, 5, 2] = value, value, 0.25
+    dw = _run(L, x, w, dy)[2]
+    t = [torch.from_numpy(np.ascontiguousarray(a)).double() for a in (x, dy)]
+    ref = torch.nn.grad.conv2d_weight(t[0], w.shape, t[1], L.stride, L.pad).numpy()
+    ref[np.abs(ref) > np.finfo(np.float32).max] = np.inf * np.sign(ref[np.abs(ref) > np.finfo(np.float32).max])
+    assert np.array_equal(np.isnan(dw), np.isnan(ref)) and np.array_equal(dw[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
+    fin = np.isfinite(ref)
+    big = fin & (np.abs(ref) > 1e30)   # the sums that the large value is in, and those that it is not in
+    for m in (big, fin & ~big):
+        if m.any():
+            assert np.max(np.abs(dw[m] - ref[m])) <= 1e-5 * np.max(np.abs(ref[m]))
