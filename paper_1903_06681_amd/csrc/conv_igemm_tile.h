@@ -87,9 +87,10 @@ hipError_t launch_tile_f32(const IgemmArgs& a, hipStream_t s);
 // take the channel chunks in turn, each with its own staging buffers, and are
 // added at the end: twice the waves per SIMD and half the chain where a layer
 // has too few blocks for two workgroups per CU.
-template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG>
-__global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
+// RAW: the sweep in plain fp32 that follows where the parts do not hold a value
+// (see the end); false returned: none is needed.
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG, bool RAW>
+__device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned char* smem) {
     static_assert(WO * WP == 4, "four waves");
     static_assert(NS == 1 || WM == kWGather, "fp32 weights are gathered");
     constexpr int OB = 32 * NOBW * WO, CC = 8 * CCG, NPH = BP ? 4 : 1;
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
     // pixel block in turn on the same XCD (its patch comes from one L2)
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int ob = idx % a.tnob, pbk = (idx / a.tnob) * 8 + xcd;
-    if (pbk >= a.tnpb) return;
+    if (pbk >= a.tnpb) return false;
     const int per = a.tnub * a.nvb;
     const int z = pbk / per, inb = pbk - z * per;
     const int ub = inb / a.nvb, vb = inb - ub * a.nvb;
@@ -196,8 +197,8 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
     // would come on top of plans that allot the whole LDS); the chunk loop's barriers
     // part this store from any other
     uint32_t* redo = reinterpret_cast<uint32_t*>(smem + a.lds_bytes - kTileRedoBytes);
-    if (NS == 3 && threadIdx.x == 0) *redo = 0;
-    // Plain fp32 (rawc): the eight channels of a record as fp32 words in its first two
+    if (NS == 3 && !RAW && threadIdx.x == 0) *redo = 0;
+    // RAW: the eight channels of a record as fp32 words in its first two
     // parts; the third part's first word marks the patch pixels and the output channels
     // that hold a value the parts do not.
     auto patch_mark = [&](int pixel) __attribute__((always_inline)) {
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         r1 = uint4{w[4], w[5], w[6], w[7]};
         return tiny;
     };
-    auto store_patch = [&](auto rawc, const uint4 (&v)[8], int slot, int col) __attribute__((always_inline)) {
+    auto store_patch = [&](const uint4 (&v)[8], int slot, int col) __attribute__((always_inline)) {
         if (slot < 0) return;
         const int step = PSU, odd = de ? (ROW / 2) * PSU : 0;
         if constexpr (NS == 1) {
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             for (int i = 0; i < 4; ++i) {
                 const float g[8] = {f[0][i], f[1][i], f[2][i], f[3][i], f[4][i], f[5][i], f[6][i], f[7][i]};
                 const int at = slot + (de ? (i / 2) * step + (i & 1) * odd : i * step);
-                if constexpr (decltype(rawc)::value) {
+                if constexpr (RAW) {
                     if (put_raw(g, pl[at], pl[at + CCG])) *patch_mark(at / PSU) = 1;
                 } else {
                     uint4 p[3];
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             else v[j] = __builtin_amdgcn_raw_buffer_load_b32(rw, b, 0, 0);
         }
     };
-    auto store_g = [&](auto rawc, const u32 (&v)[8], int slot) __attribute__((always_inline)) {
+    auto store_g = [&](const u32 (&v)[8], int slot) __attribute__((always_inline)) {
         if (slot < 0) return;
         if constexpr (NS == 1) {
             uint4 r;
@@ -300,7 +301,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             float f[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = __builtin_bit_cast(float, v[j]);
-            if constexpr (decltype(rawc)::value) {
+            if constexpr (RAW) {
                 if (put_raw(f, wl[slot], wl[slot + WPL])) *weight_mark(slot % TREC % GREC) = 1;
             } else {
                 uint4 p[3];
@@ -355,18 +356,17 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
 #pragma unroll
         for (int q = 0; q < UPT; ++q) load_patch(xs[q], poff[q], c0);
     };
-    auto store_chunk = [&](auto rawc, int c0) __attribute__((always_inline)) {
-        constexpr bool RAW = decltype(rawc)::value;   // holds nothing in registers
-        if constexpr (!RAW) {
+    auto store_chunk = [&](int c0) __attribute__((always_inline)) {
+        if constexpr (!RAW) {   // RAW holds nothing in registers
             if constexpr (WM == kWGather) {
 #pragma unroll
-                for (int q = 0; q < WPT; ++q) store_g(rawc, gs[q], wslot[q]);
+                for (int q = 0; q < WPT; ++q) store_g(gs[q], wslot[q]);
             } else {
 #pragma unroll
                 for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q]);
             }
 #pragma unroll
-            for (int q = 0; q < UPT; ++q) store_patch(rawc, xs[q], pslot[q], pcol[q]);
+            for (int q = 0; q < UPT; ++q) store_patch(xs[q], pslot[q], pcol[q]);
         }
         // units beyond the registers' share
         for (int e = tid + (RAW ? 0 : WPT) * kTileThreads; e < nwu; e += kTileThreads) {
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             if constexpr (WM == kWGather) {
                 u32 v[8];
                 load_g(v, off, cg, c0);
-                store_g(rawc, v, slot);
+                store_g(v, slot);
             } else {
                 uint4 v[WV];
                 load_w(v, off, cg, c0);
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             patch_unit(e, off, slot, col);
             uint4 v[8];
             load_patch(v, off, c0);
-            store_patch(rawc, v, slot, col);
+            store_patch(v, slot, col);
         }
     };
 
@@ -410,8 +410,8 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         return (tr * ROW + (de ? (c >> 1) + (c & 1) * (ROW / 2) : c)) * PSU;
     };
     // one k-step: records ar of the weights, br of the patch (per lane half)
-    auto kstep = [&](auto rawc, int ar, int br, bool zero, floatx16 (&c)[NOBW][NPBW]) __attribute__((always_inline)) {
-        constexpr int NR = decltype(rawc)::value ? 2 : NS;
+    auto kstep = [&](int ar, int br, bool zero, floatx16 (&c)[NOBW][NPBW]) __attribute__((always_inline)) {
+        constexpr int NR = RAW ? 2 : NS;
         uint4 A[NR][NOBW], B[NR][NPBW];
 #pragma unroll
         for (int s = 0; s < NR; ++s) {
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
                 if (zero) B[s][j] = uint4{0, 0, 0, 0};
             }
         }
-        if constexpr (decltype(rawc)::value) {
+        if constexpr (RAW) {
             // two channels an instruction, one of each half's group
             static_for<0, 8>([&](auto kc) __attribute__((always_inline)) {
                 constexpr int k = decltype(kc)::value;
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
     const int cin = a.Tr > 0 ? a.Cin : 0;   // an output phase without taps is zero
     constexpr int STEP = KG * CC;
     // the whole reduction: all channel chunks into acc
-    auto sweep = [&](auto rawc) __attribute__((always_inline)) {
+    auto sweep = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int ph = 0; ph < NPH; ++ph)
 #pragma unroll
@@ -466,15 +466,14 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
                 for (int j = 0; j < NPBW; ++j)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[ph][i][j][e] = 0.f;
-        constexpr bool AHEAD = !decltype(rawc)::value;
-        if (AHEAD && kg * CC < cin) load_chunk(kg * CC);
+        if (!RAW && kg * CC < cin) load_chunk(kg * CC);
         for (int c1 = 0; c1 < cin; c1 += STEP) {
             const int c0 = c1 + kg * CC;
             const bool mine = KG == 1 || c0 < cin;
             if (c1 > 0) __syncthreads();
-            if (mine) store_chunk(rawc, c0);
+            if (mine) store_chunk(c0);
             __syncthreads();
-            if (AHEAD && c0 + STEP < cin) load_chunk(c0 + STEP);
+            if (!RAW && c0 + STEP < cin) load_chunk(c0 + STEP);
             if (!mine) continue;
             const int ng = min(CCG, (a.Cin - c0 + 7) / 8);   // channel groups of this chunk
 #pragma unroll
@@ -489,7 +488,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
                         const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
 #pragma unroll
                         for (int g = 0; g + 1 < CCG; g += 2)
-                            if (g + 1 < ng) kstep(rawc, ao + (g + hi) * GREC, bo + g + hi, false, acc[ph]);
+                            if (g + 1 < ng) kstep(ao + (g + hi) * GREC, bo + g + hi, false, acc[ph]);
                     }
                 if (ng & 1) {
                     // a last lone group: two taps per k-step, one per half of the lanes
@@ -500,7 +499,7 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
                         if (i + 1 < nt && ++ts2 == nts) { ts2 = 0; ++tr2; }
                         const int tr = hi ? tr2 : tr1, ts = hi ? ts2 : ts1;
                         const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
-                        kstep(rawc, ao + g * GREC, bo + g, (i + 1 >= nt) & hi, acc[ph]);
+                        kstep(ao + g * GREC, bo + g, (i + 1 >= nt) & hi, acc[ph]);
                         tr1 = tr2; ts1 = ts2;
                         if (++ts1 == nts) { ts1 = 0; ++tr1; }
                     }
@@ -537,9 +536,6 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
             });
         }
     };
-    sweep(std::false_type{});
-    join();
-
     // D of a 32x32 tile: value e of lane l is row 8*(e/4) + 4*(l/32) + e%4
     // (output channel), column l%32 (pixel)
     const int oplane = a.out_rows * a.out_cols;
@@ -585,79 +581,98 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         }
     }
     };
-    if (kg == 0) {
-        if (a.nt) finish(std::integral_constant<int, kTileNT>{});
-        else finish(std::integral_constant<int, 0>{});
-    }
-    if constexpr (NS == 3) {
-        // Values the parts cannot hold: below 2^-110 noticed while staging, and too large
-        // ones, infinities and NaN by what they leave in a sum.  The block is then swept
-        // once more in plain fp32, and the outputs that such a value reaches, no others,
-        // are replaced: an output's bits depend on its own window and weights only.  The
-        // fp32 instruction and staging without loads ahead take two to four times the
-        // first sweep (128 -> 128 3x3 on a 64x64 tile: 31 us plain, 68 with one such value
-        // a tensor, 101 with nothing else; a scalar loop per output took 1,490).
-        float odd = 0.f;   // NaN where a sum is not finite
-        static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
-            constexpr int t = decltype(tc)::value;
+    if constexpr (!RAW) {
+        sweep();
+        join();
+        bool again = false;
+        if constexpr (NS == 3) {
+            float odd = 0.f;   // NaN where a sum is not finite
+            static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
+                constexpr int t = decltype(tc)::value;
+                float q[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 16; ++e) odd = fmaf(acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW][e], 0.f, odd);
-        });
-        if (range.outside() || (kg == 0 && !(odd == 0.f))) *redo = 1;
-        __syncthreads();
-        if (!*redo) return;
-        uint32_t bad[NPH][NOBW][NPBW];
-        static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
-            constexpr int t = decltype(tc)::value;
-            uint32_t& b = bad[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW];
-            b = 0;
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                b |= isfinite(acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW][e]) ? 0u : 1u << e;
-        });
-        __threadfence();   // the stores above come before those below
+                for (int e = 0; e < 16; ++e) q[e % 4] = fmaf(acc[t / (NOBW * NPBW)][t / NPBW % NOBW][t % NPBW][e], 0.f, q[e % 4]);
+                odd += (q[0] + q[1]) + (q[2] + q[3]);
+            });
+            if (range.outside() || (kg == 0 && !(odd == 0.f))) *redo = 1;
+            __syncthreads();   // before the stores, which it would wait for
+            again = *redo;
+        }
+        if (kg == 0) {
+            if (a.nt) finish(std::integral_constant<int, kTileNT>{});
+            else finish(std::integral_constant<int, 0>{});
+        }
+        return again;
+    } else {
+        __threadfence();   // the stores of the first sweep are read back below
         for (int e = tid; e < PR * ROW; e += kTileThreads) *patch_mark(e) = 0;
         for (int e = tid; e < OB; e += kTileThreads) *weight_mark(e) = 0;
         __syncthreads();
-        sweep(std::true_type{});
+        sweep();
         __syncthreads();
-        for (int k = 0; k < KG; ++k) {   // the groups' marks
+        uint32_t marks[NPH][NPBW] = {}, rows[NOBW] = {};   // of this lane's pixels and output channels
+        for (int k = 0; k < KG; ++k) {                     // marked in any group's chunks
             const uint4* wk = reinterpret_cast<uint4*>(smem) + k * a.tgrec;
             const uint4* pk = wk + NS * T * TREC;
-            uint32_t rows[NOBW];
 #pragma unroll
-            for (int i = 0; i < NOBW; ++i) {
-                rows[i] = 0;
+            for (int i = 0; i < NOBW; ++i)
+#pragma unroll
                 for (int e = 0; e < 16; ++e)
                     rows[i] |= wk[2 * WPL + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4].x ? 1u << e : 0u;
-            }
-            static_for<0, NPH * NPBW>([&](auto tc) __attribute__((always_inline)) {
-                constexpr int ph = decltype(tc)::value / NPBW, j = decltype(tc)::value % NPBW;
+#pragma unroll
+            for (int ph = 0; ph < NPH; ++ph) {
                 const int py = ph >> 1, px = ph & 1;
                 const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
                 const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
-                uint32_t mark = 0;
                 for (int tr = 0; tr < ntr; ++tr)
-                    for (int ts = 0; ts < nts; ++ts) mark |= pk[tap_b(dr + tr, dcol + ts) + pix[j] + 2 * CCG].x;
+                    for (int ts = 0; ts < nts; ++ts)
 #pragma unroll
-                for (int i = 0; i < NOBW; ++i) bad[ph][i][j] |= mark ? 0xffffu : rows[i];
-            });
+                        for (int j = 0; j < NPBW; ++j) marks[ph][j] |= pk[tap_b(dr + tr, dcol + ts) + pix[j] + 2 * CCG].x;
+            }
         }
         join();
-        if (kg != 0) return;
-        static_for<0, NPH * NOBW * NPBW>([&](auto tc) __attribute__((always_inline)) {
-            constexpr int ph = decltype(tc)::value / (NOBW * NPBW), i = decltype(tc)::value / NPBW % NOBW, j = decltype(tc)::value % NPBW;
-            const int p = (wp * NPBW + j) * 32 + l32;
-            const int ul = div16(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
-            const int orow = u * a.ostr + (BP ? ph >> 1 : a.oph_r), ocol = v * a.ostr + (BP ? ph & 1 : a.oph_c);
-            if (p >= np || v >= a.Vo || orow >= a.out_rows || ocol >= a.out_cols) return;
+        if (kg != 0) return false;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int o = o0 + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4;
-                if ((bad[ph][i][j] >> e & 1) && o < a.Cout)
-                    out[int64_t(o) * oplane + int64_t(orow) * a.out_cols + ocol] = acc[ph][i][j][e];
+        for (int ph = 0; ph < NPH; ++ph)
+#pragma unroll
+            for (int j = 0; j < NPBW; ++j) {
+                const int p = (wp * NPBW + j) * 32 + l32;
+                const int ul = div16(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
+                const int orow = u * a.ostr + (BP ? ph >> 1 : a.oph_r), ocol = v * a.ostr + (BP ? ph & 1 : a.oph_c);
+                if (p >= np || v >= a.Vo || orow >= a.out_rows || ocol >= a.out_cols) continue;
+#pragma unroll
+                for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int o = o0 + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4;
+                        if (o >= a.Cout) continue;
+                        float* q = out + int64_t(o) * oplane + int64_t(orow) * a.out_cols + ocol;
+                        if (marks[ph][j] || (rows[i] >> e & 1) || !isfinite(*q)) *q = acc[ph][i][j][e];
+                    }
             }
-        });
+        return false;
+    }
+}
+
+// fp32: values the parts cannot hold are noticed while staging (below 2^-110) or by
+// what they leave in a sum (too large ones, infinities, NaN).  The block is then
+// swept once more on the fp32 instruction, and the outputs that such a value
+// reaches, no others, are replaced: an output's bits depend on its own window and
+// weights only.  128 -> 128 3x3 on a 64x64 tile: 30 us plain, 73 with one such value
+// a tensor, 102 with nothing else; a scalar loop per output took 1,490.
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG>
+__global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const bool again = igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, false>(a, smem);
+    if constexpr (NS == 3) {
+        if (!again) return;
+        // the arguments read again: kept from the first sweep, the scalars that both
+        // derive from them do not fit (159 spilled: the four-phase kernels took 18.6 us
+        // instead of 15.6, 32 channels on a 512x512 tile)
+        auto args = __builtin_amdgcn_kernarg_segment_ptr();   // constant address space: scalar loads
+        asm volatile("" : "+s"(args));
+        const IgemmArgs b = *(const IgemmArgs*)args;
+        igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, true>(b, smem);
     }
 }
 
