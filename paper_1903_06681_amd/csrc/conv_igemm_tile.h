@@ -86,13 +86,15 @@ hipError_t launch_tile_f32(const IgemmArgs& a, hipStream_t s);
 // two column phases leave as 8-byte stores).  KG: groups of four waves that
 // take the channel chunks in turn, each with its own staging buffers, and are
 // added at the end: twice the waves per SIMD and half the chain where a layer
-// has too few blocks for two workgroups per CU.
+// has too few blocks for two workgroups per CU.  SEP: the small part products
+// of fp32 have sums of their own (see the plan).
 // RAW: the sweep in plain fp32 that follows where the parts do not hold a value
 // (see the end); false returned: none is needed.
-template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG, bool RAW>
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG, bool SEP, bool RAW>
 __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned char* smem) {
     static_assert(WO * WP == 4, "four waves");
     static_assert(NS == 1 || WM == kWGather, "fp32 weights are gathered");
+    static_assert(!SEP || (NS == 3 && KG == 1 && !RAW), "small part products apart: fp32, one group of waves");
     constexpr int OB = 32 * NOBW * WO, CC = 8 * CCG, NPH = BP ? 4 : 1;
     constexpr int ES = NS == 1 ? 2 : 4;
     constexpr int GW = 16 / ES;             // pixels of a staged 16-byte vector
@@ -394,6 +396,7 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
     };
 
     floatx16 acc[NPH][NOBW][NPBW];
+    floatx16 small[SEP ? NPH : 1][SEP ? NOBW : 1][SEP ? NPBW : 1];   // SEP: sums of the small part products
 
     // this lane's pixels (past the block's last: a repeat of it, never stored)
     const int np = bu * bv;
@@ -410,7 +413,8 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
         return (tr * ROW + (de ? (c >> 1) + (c & 1) * (ROW / 2) : c)) * PSU;
     };
     // one k-step: records ar of the weights, br of the patch (per lane half)
-    auto kstep = [&](int ar, int br, bool zero, floatx16 (&c)[NOBW][NPBW]) __attribute__((always_inline)) {
+    auto kstep = [&](int ar, int br, bool zero, int ph) __attribute__((always_inline)) {
+        floatx16 (&c)[NOBW][NPBW] = acc[ph];
         constexpr int NR = RAW ? 2 : NS;
         uint4 A[NR][NOBW], B[NR][NPBW];
 #pragma unroll
@@ -447,10 +451,12 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
 #pragma unroll
                 for (int i = 0; i < NOBW; ++i)
 #pragma unroll
-                    for (int j = 0; j < NPBW; ++j)
-                        c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    for (int j = 0; j < NPBW; ++j) {
+                        floatx16& d = SEP && k + 1 < NP ? small[SEP ? ph : 0][SEP ? i : 0][SEP ? j : 0] : c[i][j];
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                             __builtin_bit_cast(bf16x8, A[NS == 1 ? 0 : pa[k]][i]),
-                            __builtin_bit_cast(bf16x8, B[NS == 1 ? 0 : pb[k]][j]), c[i][j], 0, 0, 0);
+                            __builtin_bit_cast(bf16x8, B[NS == 1 ? 0 : pb[k]][j]), d, 0, 0, 0);
+                    }
         }
     };
 
@@ -465,7 +471,10 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
 #pragma unroll
                 for (int j = 0; j < NPBW; ++j)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[ph][i][j][e] = 0.f;
+                    for (int e = 0; e < 16; ++e) {
+                        acc[ph][i][j][e] = 0.f;
+                        if constexpr (SEP) small[ph][i][j][e] = 0.f;
+                    }
         if (!RAW && kg * CC < cin) load_chunk(kg * CC);
         for (int c1 = 0; c1 < cin; c1 += STEP) {
             const int c0 = c1 + kg * CC;
@@ -488,7 +497,7 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
                         const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
 #pragma unroll
                         for (int g = 0; g + 1 < CCG; g += 2)
-                            if (g + 1 < ng) kstep(ao + (g + hi) * GREC, bo + g + hi, false, acc[ph]);
+                            if (g + 1 < ng) kstep(ao + (g + hi) * GREC, bo + g + hi, false, ph);
                     }
                 if (ng & 1) {
                     // a last lone group: two taps per k-step, one per half of the lanes
@@ -499,7 +508,7 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
                         if (i + 1 < nt && ++ts2 == nts) { ts2 = 0; ++tr2; }
                         const int tr = hi ? tr2 : tr1, ts = hi ? ts2 : ts1;
                         const int ao = ((r0 + rs * tr) * a.S + s0 + ss * ts) * TREC, bo = tap_b(dr + tr, dcol + ts);
-                        kstep(ao + g * GREC, bo + g, (i + 1 >= nt) & hi, acc[ph]);
+                        kstep(ao + g * GREC, bo + g, (i + 1 >= nt) & hi, ph);
                         tr1 = tr2; ts1 = ts2;
                         if (++ts1 == nts) { ts1 = 0; ++tr1; }
                     }
@@ -583,6 +592,16 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
     };
     if constexpr (!RAW) {
         sweep();
+        if constexpr (SEP) {
+#pragma unroll
+            for (int ph = 0; ph < NPH; ++ph)
+#pragma unroll
+                for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                    for (int j = 0; j < NPBW; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[ph][i][j][e] += small[ph][i][j][e];
+        }
         join();
         bool again = false;
         if constexpr (NS == 3) {
@@ -660,10 +679,10 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
 // reaches, no others, are replaced: an output's bits depend on its own window and
 // weights only.  128 -> 128 3x3 on a 64x64 tile: 30 us plain, 73 with one such value
 // a tensor, 102 with nothing else; a scalar loop per output took 1,490.
-template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG>
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG, bool SEP>
 __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const bool again = igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, false>(a, smem);
+    const bool again = igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, SEP, false>(a, smem);
     if constexpr (NS == 3) {
         if (!again) return;
         // the arguments read again: kept from the first sweep, the scalars that both
@@ -672,13 +691,13 @@ __global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmA
         auto args = __builtin_amdgcn_kernarg_segment_ptr();   // constant address space: scalar loads
         asm volatile("" : "+s"(args));
         const IgemmArgs b = *(const IgemmArgs*)args;
-        igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, true>(b, smem);
+        igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, false, true>(b, smem);
     }
 }
 
-template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG = 1>
+template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG = 1, bool SEP = false>
 static hipError_t launch_tile(const IgemmArgs& a, hipStream_t s) {
-    auto k = igemm_tile_kernel<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG>;
+    auto k = igemm_tile_kernel<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, SEP>;
     if (a.lds_bytes > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);

@@ -58,11 +58,21 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
     const int64_t nominal = int64_t(a.Nn) * ((int64_t(a.Uo) * a.Vo + 127) / 128) * ((a.Cout + 63) / 64);
     const bool pair = nominal <= (a.bp ? cus / 2 : cus) && nchunk >= 4 &&
                       (NS == 3 ? ccg == 2 : ccg == 4 && (wm == kWBlocks || (wm == kWRows && T == 9)));
+    // fp32 on few channels: a group of eight that is mostly empty makes six additions
+    // of one or a few products, each rounded at the size of the sum, where the fp32
+    // instruction makes one for every two channels.  The five small part products of
+    // each k-step then have sums of their own, added at the end.  Error of y against 64
+    // bits (fp32 instruction, one sum, two sums): 3 -> 16 channels 3x3 stride 2 9.6e-8,
+    // 1.2e-7, 3.9e-8; 17 -> 9 2.2e-7, 2.4e-7, 7.6e-8, in the same time.  From 19 channels
+    // on, whole groups make fewer additions than the fp32 instruction (32 channels 3.0e-7,
+    // 2.5e-7), and 64 x 128 blocks, whose registers do not hold second sums, are worth having.
+    a.tsep = NS == 3 && !a.bp && a.Cin <= 18;
     double best = 0;
     bool found = false;
     for (int kg = pair ? 2 : 1; kg >= 1 && !found; --kg)
     for (int c = 0; c < nc; ++c) {
         const Cfg& f = cfgs[c];
+        if (a.tsep && f.id == 1) continue;
         if (kg == 2 && NS == 1 && !a.bp && (f.id == 0 || f.id == 4)) continue;
         if (wm == kWGather && NS == 1 && !a.bp && (f.id == 0 || f.id == 4)) continue;
         const int nob = (a.Cout + f.OB - 1) / f.OB;

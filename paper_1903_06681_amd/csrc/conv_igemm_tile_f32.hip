@@ -9,6 +9,11 @@ hipError_t launch_tile_f32(const IgemmArgs& a, hipStream_t s) {
         constexpr int OB = 32 * nob * wo; \
         if (a.tkg == 2 && a.tccg == 2) return launch_tile<3, 2, nob, npb, wo, wp, kWGather, 1, OB == 32 ? 3 : 5, 1, BPH, 2>(a, s); \
         if (a.tkg != 1) return hipErrorInvalidValue; \
+        if constexpr (!BPH && id != 1) { \
+            if (a.tsep && a.tccg == 2) return launch_tile<3, 2, nob, npb, wo, wp, kWGather, 1, OB == 32 ? 3 : 5, 2, false, 1, true>(a, s); \
+            if (a.tsep && a.tccg == 4) return launch_tile<3, 4, nob, npb, wo, wp, kWGather, 1, 1, 2, false, 1, true>(a, s); \
+        } \
+        if (a.tsep) return hipErrorInvalidValue; \
         if (a.tccg == 2) return launch_tile<3, 2, nob, npb, wo, wp, kWGather, 1, OB == 32 ? 3 : 5, BPH ? 1 : 2, BPH>(a, s); \
         if (a.tccg == 4) return launch_tile<3, 4, nob, npb, wo, wp, kWGather, 1, 1, BPH ? 1 : 2, BPH>(a, s); \
     }

@@ -98,6 +98,7 @@ struct IgemmArgs {
     // of a cell may choose the arithmetic of its block
     int sr0, sr1, sc0, sc1;
     int own;                     // interior launch: width of the margins, which no stored output reads
+    int tsep;                    // fp32: the small part products have sums of their own
     int tkg, tgrec;              // groups of waves that share the channel chunks (1 or 2), their LDS records
     int nt;                      // outputs leave by non-temporal stores (blocked, rolling-row kernels)
     uint32_t tmt, tmpg, tmbv, tmnf;   // 2^32 / d + 1 of the kernel's divisors (0 for 1)

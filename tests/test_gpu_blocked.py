@@ -224,3 +224,19 @@ def test_fp32_weight_gradient_with_values_the_parts_do_not_hold(L, value):
     for m in (big, fin & ~big):
         if m.any():
             assert np.max(np.abs(dw[m] - ref[m])) <= 1e-5 * np.max(np.abs(ref[m]))
+
+
+@pytest.mark.parametrize("C,K,R", [(3, 16, 3), (4, 72, 3), (9, 48, 3), (17, 9, 3), (18, 40, 3), (3, 64, 5), (9, 33, 1), (18, 64, 1)])
+def test_fp32_few_channels_keep_their_accuracy(C, K, R):
+    """Channel groups that are mostly empty do not cost additions at the size of the sum:
+    each k-step (16 channels of a tap, or 8 of two) rounds there once, by at most 2^-24 of a
+    partial sum, 2^-24 / sqrt(3) on average, and partial sums grow as the root of the steps:
+    the k-steps together sqrt(steps / 2) of that, the last addition one more."""
+    L = Layer("few", 2, C, K, 90, 86, R, R, 2, R // 2, 1, 1, R // 2, "f32", "normal", 950 + C)
+    print(f"[few] {_id(L)}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    y = _run(L, x, w, dy)[0]
+    groups = (C + 7) // 8
+    steps = groups // 2 * R * R + groups % 2 * ((R * R + 1) // 2)
+    err = _rel(y, orc.conv_fwd(x, w, L.stride, L.pad))
+    assert err <= 2.0 ** -24 / 3 ** 0.5 * (steps / 2 + 1) ** 0.5, err
