@@ -144,14 +144,24 @@ static int64_t rows_lds(int dtype, int C, int R, int S, int istr) {
 }
 
 static bool make_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, int stride,
-                      int Hot, int Wot, int base_c, int dy_off, Plan* pl) {
+                      int Hot, int Wot, int base_c, int dy_off, Plan* pl, bool tile = true) {
     std::memset(pl, 0, sizeof(*pl));
     // what the row kernels cannot stage (filters over 7 wide in bf16, strides of
     // about 7 and more) is refused, whichever kernel would run
     const bool stageable = !(dtype == 1 && S > 7) && rows_lds(dtype, C, R, S, stride) <= device_lds_limit();
     auto blocked = [&]() {
-        if (!stageable) return false;
+        if (!stageable || !tile) return false;
         if (!wgrad_tile_plan(dtype, ntiles, N, C, K, R, S, stride, Hot, Wot, base_c, dy_off, &pl->tile)) return false;
+        // One chunk of whole channel blocks past the allocation-free entry point's
+        // array, where the other kernels' partials fit it: theirs, slower, so that what
+        // that entry point takes does not depend on the block shape.
+        const int64_t most = int64_t(wgrad_scratch_capacity());
+        if (pl->tile.nchunks * pl->tile.F * 4 > most) {
+            Plan other;
+            if (make_plan(dtype, ntiles, N, C, K, R, S, stride, Hot, Wot, base_c, dy_off, &other, false) &&
+                other.nchunks * other.F * 4 <= most)
+                return false;
+        }
         pl->kind = WGRAD_TILE;
         pl->gy = pl->tile.gy; pl->gz = pl->tile.gz; pl->nchunks = pl->tile.nchunks; pl->F = pl->tile.F;
         pl->nqb = pl->tile.nqb;
@@ -292,7 +302,7 @@ bool wgrad_plan(WgradArgs& a, int dtype) {
     a.F = pl.F; a.frag = pl.frag;
     if (a.kind == WGRAD_TILE) {
         const WgradTile& t = pl.tile;
-        a.tcfg = t.tcfg; a.tnow = t.now; a.tncw = t.ncw; a.two = t.wo; a.twc = t.wc; a.ttw = t.tw; a.tnws = t.nws;
+        a.tcfg = t.tcfg; a.tnow = t.now; a.tncw = t.ncw; a.two = t.wo; a.twc = t.wc;
         a.tbu = t.tbu; a.tbv = t.tbv; a.tnub = t.tnub; a.tnpb = t.tnpb; a.tbpc = t.tbpc;
         a.tpg = t.tpg; a.tdg = t.tdg; a.tnbuf = t.tnbuf;
         a.tmpg = t.tmpg; a.tmdg = t.tmdg; a.tmbv = t.tmbv;

@@ -438,18 +438,20 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
             join();
         }
     }
-    // partial: [chunk][gy][gz][wave][tap][o block][c block][4][64 lanes][4]; value j of
-    // lane l in quarter q is row 8 q + 4 (l/32) + j (filter), column l%32 (channel)
+    // partial: [chunk][gz][tap][wave of the tap][o block][c block][4][64 lanes][4], the
+    // filter's taps only; value j of lane l in quarter q is row 8 q + 4 (l/32) + j
+    // (filter), column l%32 (channel)
     if (wk > 0) return;
+    constexpr int NB = NOW * NCW;
     float* part = a.part + int64_t(blockIdx.x) * a.F +
-                  ((int64_t(blockIdx.y) * a.gz + blockIdx.z) * NWS + wsub) * NBW * 1024;
+                  ((int64_t(blockIdx.z) * T + tap0) * (WO * WC) + wo * WC + wc) * NB * 1024;
     static_for<0, NBW>([&](auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
-        if (tap0 + i / (NOW * NCW) >= T) return;
-        const floatx16& v = acc[i / (NOW * NCW)][i / NCW % NOW][i % NCW];
+        if (tap0 + i / NB >= T) return;
+        const floatx16& v = acc[i / NB][i / NCW % NOW][i % NCW];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            reinterpret_cast<f32x4*>(part)[i * 256 + q * 64 + lane] =
+            reinterpret_cast<f32x4*>(part)[(i / NB * (WO * WC) * NB + i % NB) * 256 + q * 64 + lane] =
                 f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
     });
 }

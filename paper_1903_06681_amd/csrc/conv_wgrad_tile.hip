@@ -77,12 +77,12 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
     }
     if (!found) return false;
     t->tcfg = id;
-    t->now = f.now; t->ncw = f.ncw; t->wo = f.wo; t->wc = f.wc; t->tw = f.tw; t->nws = nws;
+    t->now = f.now; t->ncw = f.ncw; t->wo = f.wo; t->wc = f.wc;
     t->gy = (T + f.wt * f.tw - 1) / (f.wt * f.tw);
     t->gz = ((K + OBK - 1) / OBK) * ((C + CBK - 1) / CBK);
-    t->F = int64_t(t->gy) * t->gz * nws * nbw * 1024;
-    // Chunks: at most one workgroup per CU and 64 MiB of partials (what the
-    // allocation-free entry point holds); more of them shorten the walk over the
+    t->F = int64_t(t->gz) * T * f.wo * f.wc * f.now * f.ncw * 1024;
+    // Chunks: at most one workgroup per CU, and 64 MiB of partials (what the
+    // allocation-free entry point holds) where one chunk's stay below it; more of them shorten the walk over the
     // pixel blocks (matrix work and about 1 us of barriers and exposed latency
     // each), fewer move less: each chunk writes and reads F floats at about
     // 10 TB/s.  Above eight a whole number per XCD, so that the blocks of one chunk
@@ -110,23 +110,21 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
 // 32 x 32 block, so that the block's place is scalar arithmetic and each
 // thread moves four filters' values with 16-byte loads.  Bound: HBM (the
 // partials); where the quarters leave CUs idle the round trips of one thread,
-// hence sixteen groups from 32 chunks on (us: 256 chunks of 40 quarters, fp32
+// hence sixteen groups from 32 chunks on (us: 256 chunks of 36 quarters, fp32
 // 32 -> 32 stride 2 on a 512x512 tile, 8.9 with four groups, 6.7 with sixteen;
-// 64 chunks of 640 quarters 8.4 and 11.7).
+// 64 chunks of 576 quarters 8.4 and 11.7).
 template <int G>
 __global__ __launch_bounds__(64 * G) void wgrad_tile_reduce_kernel(WgradArgs a) {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     __shared__ f32x4 red[G][64];
     const int q = blockIdx.x & 3, blk = blockIdx.x >> 2, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int nbw = a.ttw * a.tnow * a.tncw;
-    const int b = blk % nbw, w = blk / nbw, wsub = w % a.tnws, zz = w / a.tnws;
-    const int bz = zz % a.gz, by = zz / a.gz;
-    const int wt = wsub / (a.two * a.twc), wo = wsub / a.twc % a.two, wc = wsub % a.twc;
-    const int nwt = a.tnws / (a.two * a.twc), cbk = 32 * a.tncw * a.twc, ncsb = (a.C + cbk - 1) / cbk;
-    const int tap = (by * nwt + wt) * a.ttw + b / (a.tnow * a.tncw), T = a.R * a.S;
+    const int nb = a.tnow * a.tncw, T = a.R * a.S;
+    const int b = blk % nb, w = blk / nb, wc = w % a.twc, wo = w / a.twc % a.two, zz = w / (a.twc * a.two);
+    const int tap = zz % T, bz = zz / T;
+    const int cbk = 32 * a.tncw * a.twc, ncsb = (a.C + cbk - 1) / cbk;
     const int o0 = (((bz / ncsb) * a.two + wo) * a.tnow + b / a.tncw % a.tnow) * 32 + 8 * q;
     const int c0 = (((bz % ncsb) * a.twc + wc) * a.tncw + b % a.tncw) * 32;
-    if (tap >= T || o0 >= a.K || c0 >= a.C) return;
+    if (o0 >= a.K || c0 >= a.C) return;
     const f32x4* src = reinterpret_cast<const f32x4*>(a.part) + int64_t(blockIdx.x) * 64 + lane;
     const int64_t step = a.F / 4;
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};

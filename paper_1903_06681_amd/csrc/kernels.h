@@ -147,12 +147,11 @@ enum WgradKind { WGRAD_STRIP_BF16 = 0, WGRAD_ROWS_BF16 = 1, WGRAD_ROWS_F32 = 2, 
                  WGRAD_TAPS2_BF16 = 4, WGRAD_F32W = 5, WGRAD_KSLICE_BF16 = 6, WGRAD_TILE = 7 };
 
 // Plan of the blocked weight gradient: instantiation (32x32 blocks per wave
-// now x ncw, waves wo x wc x taps, tw taps per wave; nws waves hold sums at
-// the end), pixel blocks of tbu x tbv (tnub x nqb per image, tnpb in all, tbpc
+// now x ncw, waves of a tap wo x wc), pixel blocks of tbu x tbv (tnub x nqb per image, tnpb in all, tbpc
 // per chunk), 16-byte vectors per staged x and dy row, staging buffers, and
 // 2^32 / d + 1 of the kernel's divisors (0 for 1).
 struct WgradTile {
-    int tcfg, now, ncw, wo, wc, tw, nws;
+    int tcfg, now, ncw, wo, wc;
     int tbu, tbv, tnub, nqb, tnpb, tbpc, tpg, tdg, tnbuf;
     int gy, gz, nchunks, lds_bytes;
     int64_t F;
@@ -189,7 +188,7 @@ struct WgradArgs {
                                  // float4 per lane; 6: the blocked kernel's)
     int lds_bytes;
     // blocked kernel (WgradTile)
-    int tcfg, tnow, tncw, two, twc, ttw, tnws;
+    int tcfg, tnow, tncw, two, twc;
     int tbu, tbv, tnub, tnpb, tbpc, tpg, tdg, tnbuf;
     uint32_t tmpg, tmdg, tmbv;
 };

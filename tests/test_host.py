@@ -281,3 +281,20 @@ def test_blocked_kernels_hold_no_static_lds(unit, tmp_path):
     notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", dev], capture_output=True, text=True, check=True).stdout
     lds = [int(v) for v in re.findall(r"\.group_segment_fixed_size:\s*(\d+)", notes)]
     assert lds and set(lds) == {0}, lds
+
+
+@pytest.mark.parametrize("kw", [
+    dict(C=1024, K=2048, R=2, S=2, stride=2, pad=0, halo=0, H=14, W=14, dtype=dc.DC_BF16),   # dw 32 MiB
+    dict(C=1344, K=1344, R=3, S=3, pad=1, H=14, W=14),                                       # 62 MiB
+    dict(C=1344, K=1344, R=3, S=3, stride=2, pad=1, H=14, W=14, dtype=dc.DC_BF16),
+    dict(C=1024, K=1024, R=4, S=4, stride=2, pad=1, halo=2, H=14, W=14, dtype=dc.DC_BF16),   # 64 MiB
+    dict(C=49, K=33945, R=2, S=2, stride=2, pad=0, halo=0, H=28, W=4, dtype=dc.DC_BF16),     # partial channel blocks
+    dict(C=205, K=15368, R=4, S=1, pad=2, halo=3, H=14, W=7),
+], ids=lambda kw: f"{kw['C']}-{kw['K']}-{kw['R']}x{kw['S']}")
+def test_noalloc_takes_layers_whose_gradient_fits_its_array(kw):
+    """One chunk of partials is never wider than the fixed array where dw itself is not:
+    block shapes (taps per wave, channels per block) do not decide what the call takes."""
+    p = prob(**dict(dict(N=2, P=1, Q=1), **kw))
+    assert dc.validate(p, 0) == 0
+    need = dc.bwd_filter_workspace_bytes(p, 0)
+    assert 4 * p.K * p.C * p.R * p.S <= need <= dc.BWD_FILTER_NOALLOC_MAX_BYTES
