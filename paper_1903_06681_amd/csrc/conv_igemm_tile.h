@@ -129,11 +129,13 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
     uint4* wl = reinterpret_cast<uint4*>(smem) + kg * a.tgrec;   // [NS][T][CCG][OB], padded
     uint4* pl = wl + NS * T * TREC;               // [PR][ROW][PSU]
     const int WPL = T * TREC;
-    const int PG = a.tpg, PR = (bu - 1) * a.istr + a.Tr;   // 8-pixel groups per row, rows
+    int istr = a.istr;
+    asm("" : "+s"(istr));   // not loaded again beside LDS writes, which the wait would drain
+    const int PG = a.tpg, PR = (bu - 1) * istr + a.Tr;   // 8-pixel groups per row, rows
     const int ROW = PG * GW;
-    const int cin0 = v0 * a.istr + a.base_c, ca = cin0 & ~(GW - 1), sh = cin0 - ca;
-    const int row0 = u0 * a.istr + a.base_r;
-    const bool de = a.istr == 2;   // even and odd columns apart
+    const int cin0 = v0 * istr + a.base_c, ca = cin0 & ~(GW - 1), sh = cin0 - ca;
+    const int row0 = u0 * istr + a.base_r;
+    const bool de = istr == 2;   // even and odd columns apart
 
     // ---- staging units of this thread
     uint32_t poff[UPT];            // patch: byte offset for channel group 0 of a chunk
@@ -313,7 +315,21 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
             }
         }
     };
-    auto store_w = [&](const uint4 (&v)[WV], int slot, int cg) __attribute__((always_inline)) {
+    // kWBlocks: unit's records held (at) or found on the way; the smallest blocks hold
+    // them (72 -> 40 channels on 93x75, three chunks: 17.8 us against 19.2), larger ones
+    // have no registers left
+    constexpr bool HOLD = WM == kWBlocks && NOBW * NPBW == 1 && !BP && CCG == 4;
+    auto w_records = [&](int slot, int cg, int (&at)[8]) __attribute__((always_inline)) {
+        int o = div16(slot, a.tmt), t = slot - o * T;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            at[i] = t * TREC + cg * GREC + o;
+            const bool wrap = ++t == T;
+            t = wrap ? 0 : t;
+            o += wrap ? 1 : 0;
+        }
+    };
+    auto store_w = [&](const uint4 (&v)[WV], int slot, int cg, const int* at) __attribute__((always_inline)) {
         if (slot < 0) return;
         if constexpr (WM == kWRows) {
             u32 d[4 * TT];
@@ -327,7 +343,7 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
             u32 d[8][4];
 #pragma unroll
             for (int j = 0; j < 8; ++j) { d[j][0] = v[j].x; d[j][1] = v[j].y; d[j][2] = v[j].z; d[j][3] = v[j].w; }
-            int o = div16(slot, a.tmt), t = slot - o * T;
+            int o = HOLD ? 0 : div16(slot, a.tmt), t = slot - o * T;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const u32 sel = (i & 1) ? 0x07060302u : 0x05040100u;
@@ -336,14 +352,23 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
                 r.y = __builtin_amdgcn_perm(d[3][i / 2], d[2][i / 2], sel);
                 r.z = __builtin_amdgcn_perm(d[5][i / 2], d[4][i / 2], sel);
                 r.w = __builtin_amdgcn_perm(d[7][i / 2], d[6][i / 2], sel);
-                wl[t * TREC + cg * GREC + o] = r;
-                const bool wrap = ++t == T;
-                t = wrap ? 0 : t;
-                o += wrap ? 1 : 0;
+                if constexpr (HOLD) {
+                    wl[at[i]] = r;
+                } else {
+                    wl[t * TREC + cg * GREC + o] = r;
+                    const bool wrap = ++t == T;
+                    t = wrap ? 0 : t;
+                    o += wrap ? 1 : 0;
+                }
             }
         }
     };
 
+    int wat[HOLD ? WPT : 1][8];
+    if constexpr (HOLD) {
+#pragma unroll
+        for (int q = 0; q < WPT; ++q) w_records(wslot[q], wcg[q], wat[q]);
+    }
     uint4 xs[UPT][8];
     uint4 ws[WM == kWGather ? 1 : WPT][WV];
     u32 gs[WM == kWGather ? WPT : 1][8];
@@ -365,7 +390,7 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
                 for (int q = 0; q < WPT; ++q) store_g(gs[q], wslot[q]);
             } else {
 #pragma unroll
-                for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q]);
+                for (int q = 0; q < WPT; ++q) store_w(ws[q], wslot[q], wcg[q], wat[HOLD ? q : 0]);
             }
 #pragma unroll
             for (int q = 0; q < UPT; ++q) store_patch(xs[q], pslot[q], pcol[q]);
@@ -382,7 +407,9 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
             } else {
                 uint4 v[WV];
                 load_w(v, off, cg, c0);
-                store_w(v, slot, cg);
+                int at[8];
+                if constexpr (HOLD) w_records(slot, cg, at);
+                store_w(v, slot, cg, at);
             }
         }
         for (int e = tid + (RAW ? 0 : UPT) * kTileThreads; e < npu; e += kTileThreads) {
@@ -405,7 +432,7 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
     for (int j = 0; j < NPBW; ++j) {
         const int p = min((wp * NPBW + j) * 32 + l32, np - 1);
         const int ul = div16(p, a.tmbv), vl = p - ul * bv;
-        pix[j] = (ul * a.istr * ROW + (de ? vl : vl * a.istr)) * PSU;
+        pix[j] = (ul * istr * ROW + (de ? vl : vl * istr)) * PSU;
     }
     const int abase = wo * 32 * NOBW + l32;
     auto tap_b = [&](int tr, int ts) __attribute__((always_inline)) {   // record offset of tap (tr, ts)
@@ -545,6 +572,49 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
             });
         }
     };
+    if constexpr (RAW) {
+        __threadfence();   // the stores of the first sweep are read back below
+        for (int e = tid; e < PR * ROW; e += kTileThreads) *patch_mark(e) = 0;
+        for (int e = tid; e < OB; e += kTileThreads) *weight_mark(e) = 0;
+        __syncthreads();
+    }
+    sweep();
+    if constexpr (SEP) {
+#pragma unroll
+        for (int ph = 0; ph < NPH; ++ph)
+#pragma unroll
+            for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                for (int j = 0; j < NPBW; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[ph][i][j][e] += small[ph][i][j][e];
+    }
+    // RAW: the marks of this lane's pixels and output channels, in any group's chunks
+    uint32_t marks[RAW ? NPH : 1][RAW ? NPBW : 1] = {}, rows[RAW ? NOBW : 1] = {};
+    if constexpr (RAW) {
+        __syncthreads();
+        for (int k = 0; k < KG; ++k) {
+            const uint4* wk = reinterpret_cast<uint4*>(smem) + k * a.tgrec;
+            const uint4* pk = wk + NS * T * TREC;
+#pragma unroll
+            for (int i = 0; i < NOBW; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    rows[i] |= wk[2 * WPL + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4].x ? 1u << e : 0u;
+#pragma unroll
+            for (int ph = 0; ph < NPH; ++ph) {
+                const int py = ph >> 1, px = ph & 1;
+                const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
+                const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
+                for (int tr = 0; tr < ntr; ++tr)
+                    for (int ts = 0; ts < nts; ++ts)
+#pragma unroll
+                        for (int j = 0; j < NPBW; ++j) marks[ph][j] |= pk[tap_b(dr + tr, dcol + ts) + pix[j] + 2 * CCG].x;
+            }
+        }
+    }
+    join();
+
     // D of a 32x32 tile: value e of lane l is row 8*(e/4) + 4*(l/32) + e%4
     // (output channel), column l%32 (pixel)
     const int oplane = a.out_rows * a.out_cols;
@@ -591,18 +661,6 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
     }
     };
     if constexpr (!RAW) {
-        sweep();
-        if constexpr (SEP) {
-#pragma unroll
-            for (int ph = 0; ph < NPH; ++ph)
-#pragma unroll
-                for (int i = 0; i < NOBW; ++i)
-#pragma unroll
-                    for (int j = 0; j < NPBW; ++j)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[ph][i][j][e] += small[ph][i][j][e];
-        }
-        join();
         bool again = false;
         if constexpr (NS == 3) {
             float odd = 0.f;   // NaN where a sum is not finite
@@ -623,33 +681,6 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
         }
         return again;
     } else {
-        __threadfence();   // the stores of the first sweep are read back below
-        for (int e = tid; e < PR * ROW; e += kTileThreads) *patch_mark(e) = 0;
-        for (int e = tid; e < OB; e += kTileThreads) *weight_mark(e) = 0;
-        __syncthreads();
-        sweep();
-        __syncthreads();
-        uint32_t marks[NPH][NPBW] = {}, rows[NOBW] = {};   // of this lane's pixels and output channels
-        for (int k = 0; k < KG; ++k) {                     // marked in any group's chunks
-            const uint4* wk = reinterpret_cast<uint4*>(smem) + k * a.tgrec;
-            const uint4* pk = wk + NS * T * TREC;
-#pragma unroll
-            for (int i = 0; i < NOBW; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    rows[i] |= wk[2 * WPL + (wo * NOBW + i) * 32 + 4 * hi + 8 * (e / 4) + e % 4].x ? 1u << e : 0u;
-#pragma unroll
-            for (int ph = 0; ph < NPH; ++ph) {
-                const int py = ph >> 1, px = ph & 1;
-                const int ntr = BP ? a.bptr[py] : a.Tr, nts = BP ? a.bpts[px] : a.Ts;
-                const int dr = BP ? a.bpdr[py] : 0, dcol = BP ? a.bpdc[px] : 0;
-                for (int tr = 0; tr < ntr; ++tr)
-                    for (int ts = 0; ts < nts; ++ts)
-#pragma unroll
-                        for (int j = 0; j < NPBW; ++j) marks[ph][j] |= pk[tap_b(dr + tr, dcol + ts) + pix[j] + 2 * CCG].x;
-            }
-        }
-        join();
         if (kg != 0) return false;
 #pragma unroll
         for (int ph = 0; ph < NPH; ++ph)
@@ -680,18 +711,21 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
 // weights only.  128 -> 128 3x3 on a 64x64 tile: 30 us plain, 73 with one such value
 // a tensor, 102 with nothing else; a scalar loop per output took 1,490.
 template <int NS, int CCG, int NOBW, int NPBW, int WO, int WP, int WM, int TT, int WPT, int UPT, bool BP, int KG, bool SEP>
-__global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmArgs a) {
+__global__ __launch_bounds__(kTileThreads * KG, 2) void igemm_tile_kernel(IgemmArgs) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const bool again = igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, SEP, false>(a, smem);
+    // the arguments where they lie (constant address space: scalar loads); a by-value
+    // parameter handed on would be loaded whole at entry
+    auto args = __builtin_amdgcn_kernarg_segment_ptr();
+    const bool again = igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, SEP, false>(
+        *(const IgemmArgs*)args, smem);
     if constexpr (NS == 3) {
         if (!again) return;
         // the arguments read again: kept from the first sweep, the scalars that both
         // derive from them do not fit (159 spilled: the four-phase kernels took 18.6 us
         // instead of 15.6, 32 channels on a 512x512 tile)
-        auto args = __builtin_amdgcn_kernarg_segment_ptr();   // constant address space: scalar loads
         asm volatile("" : "+s"(args));
-        const IgemmArgs b = *(const IgemmArgs*)args;
-        igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, false, true>(b, smem);
+        igemm_tile_sweep<NS, CCG, NOBW, NPBW, WO, WP, WM, TT, WPT, UPT, BP, KG, false, true>(
+            *(const IgemmArgs*)args, smem);
     }
 }
 

@@ -188,14 +188,14 @@ __global__ __launch_bounds__(kWtThreads, 2) void wgrad_tile_kernel(WgradArgs a) 
             }
         } else {
             // the row's first and last vectors: the pitch, and in fp32 what no sum reads, hold anything
-            const int col = u.col + k.v0 * st, c0 = NS == 1 ? 0 : a.base_c, c1 = NS == 1 ? a.x_cols : xc1;
-            if (col >= c0 && col + GW <= c1) {
+            const int col = u.col + k.v0 * st, c1 = NS == 1 ? a.x_cols : xc1;
+            if ((NS == 1 || col >= a.base_c) && c1 - col >= GW) {
 #pragma unroll
                 for (int i = 0; i < GW; ++i) put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, true);
             } else {
 #pragma unroll
                 for (int i = 0; i < GW; ++i)
-                    put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, (col + i >= c0) & (col + i < c1));
+                    put(i, (de ? (i / 2) + (i & 1) * (ROW / 2) : i) * 4, (NS == 1 || col + i >= a.base_c) & (i < c1 - col));
             }
         }
     };
