@@ -38,10 +38,12 @@ bool igemm_roll_plan(IgemmArgs& a) {
     a.rows_per_seg = best;
     a.nseg = a.Uo / best;
     a.OB = 32 * NOB;
-    // Non-temporal stores once the output is past what the caches keep for its
-    // reader: with inputs and outputs that change from call to call (c5a, 67 MB)
-    // the forward takes 29 us against 34, backward-data 25 against 30; on 34 MB
-    // (c5b, 5x5) system scope is 0.5 us faster.
+    // Non-temporal stores of large outputs: with inputs and outputs that change from
+    // call to call (c5a, 67 MB) the forward takes 26 us against 32, backward-data 24
+    // against 29; on 34 MB (c5b, 5x5) system scope is 0.5 us faster.  Part of that
+    // moves to a reader right after, which finds nothing in the caches: with a
+    // conversion of the output to bf16 behind the call, 48 us against 46 forward and
+    // 48 against 45 backward-data; on 134 MB (N = 8) 43 against 56 alone, 89 against 83.
     a.nt = NOB == 2 && int64_t(a.Nn) * a.Cout * oplane * 4 >= (int64_t(48) << 20);
     a.wvec = 1;
     a.phase = 0;

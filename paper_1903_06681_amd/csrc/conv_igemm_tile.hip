@@ -113,7 +113,10 @@ bool igemm_tile_plan(IgemmArgs& a, int dtype) {
                 a.tkg = kg; a.tgrec = int(grec);
                 // whole 64-byte sectors of a large output bypass the caches (64 -> 256 1x1
                 // on 56x56, N=32, 103 MB: 39 -> 25 us; with blocks of 196 pixels, whose
-                // sectors are shared, on 28x28: 14 -> 24)
+                // sectors are shared, on 28x28: 14 -> 24).  With a reader right after, a
+                // conversion to bf16, 60 -> 65 us there and 15.8 -> 16.7 on 26 MB; fp32 layers,
+                // slower to write, gain with it too (32 channels stride 2 input gradient on a
+                // 512x512 tile 26.6 -> 26.4, alone 18.1 -> 16.7).
                 const bool rows = a.out_cols % 16 == 0 && bv % 16 == 0;
                 const bool flat = !a.bp && a.ostr == 1 && nvb == 1 && (int64_t(a.out_rows) * a.out_cols) % 16 == 0 &&
                                   int64_t(bu) * bv % 16 == 0;

@@ -38,10 +38,9 @@ __device__ __forceinline__ void wreg_store(float* p, float v) {
 // channel), added to the row's offset; the lane's part is voff.  Written as
 // a 64-bit address expression, the per-channel offsets stayed live, ran the
 // kernel out of scalar registers and were read back from lanes of a vector
-// register (v_readlane) in front of every store.  NT: non-temporal, for the
-// stride-2 forward, whose output is many times its input (conv1 at 224^2,
-// N = 32, 103 MB, buffers changing from call to call: 62 -> 45 us; the 3x3
-// and 1x1 layers that stay on this kernel gain nothing or lose 0.4 us).
+// register (v_readlane) in front of every store.  NT: non-temporal, for large
+// outputs of the stride-2 forward (see the plan; the 3x3 and 1x1 layers that
+// stay on this kernel gain nothing or lose 0.4 us).
 template <int OC, bool NT>
 __device__ __forceinline__ void wreg_store_oc(__amdgpu_buffer_rsrc_t rs, int voff, int rowoff, int cstride, float v) {
     int so;
@@ -91,7 +90,7 @@ __device__ __forceinline__ void transpose8x8(const uint4 (&in)[8], uint4 (&out)[
 // partial; their stores stay inside the MFMA stream, masked per lane (a
 // separate instantiation, so that layers with whole strips keep exactly the
 // code they had: that kernel is sensitive to small changes in its schedule).
-template <int NOB, int TR, int TS, int CG, int MINWG, int MODE = 0, bool MF = false>
+template <int NOB, int TR, int TS, int CG, int MINWG, int MODE = 0, bool MF = false, bool NT = false>
 __global__ __launch_bounds__(kWThreads, MINWG) void igemm_wreg_kernel(IgemmArgs a) {
     constexpr bool PH = MODE == 1, BP = MODE == 2;
     constexpr int KS = TR * TS * CG;          // 16-wide k-steps: (tap, 16-channel group)
@@ -456,9 +455,9 @@ __global__ __launch_bounds__(kWThreads, MINWG) void igemm_wreg_kernel(IgemmArgs 
             const __amdgpu_buffer_rsrc_t rs = rout;
             const int vo = voff_out, ro = prow4, cs = opl4;
             if constexpr (MF) {
-                if (v < a.Vo) wreg_store_oc<oc, PH>(rs, vo, ro, cs, prev[sob][e]);
+                if (v < a.Vo) wreg_store_oc<oc, NT>(rs, vo, ro, cs, prev[sob][e]);
             } else {
-                wreg_store_oc<oc, PH>(rs, vo, ro, cs, prev[sob][e]);
+                wreg_store_oc<oc, NT>(rs, vo, ro, cs, prev[sob][e]);
             }
         };
         auto mfmas = [&](auto with_stores) {
@@ -576,6 +575,12 @@ bool igemm_wreg_plan(IgemmArgs& a) {
             const int lds = wreg_lds(NOB, TRp, TSp, 1);
             if (lds <= device_lds_limit()) {
                 a.phase = 1;
+                // Non-temporal stores from 64 MB on (conv1 at 224^2, three buffers in turn, us
+                // without and with: N = 32, 103 MB, 56.5 and 40.9; N = 16, 51 MB, 27.2 and 27.9;
+                // N = 8, 26 MB, 22.4 and 23.2; on a 2x2 grid, 26 MB, 23.0 and 23.4).  A reader
+                // right after fetches the output from HBM then: with a conversion of y to bf16
+                // behind the call, 84 and 87 us at N = 32.
+                a.nt = int64_t(a.Nn) * a.Cout * a.out_rows * a.out_cols * 4 >= (int64_t(64) << 20);
                 a.Tr = TRp; a.Ts = TSp;
                 a.OB = NOB * 32;
                 a.wvec = 0;
@@ -610,11 +615,11 @@ bool igemm_wreg_plan(IgemmArgs& a) {
     return true;
 }
 
-template <int NOB, int TR, int TS, int CG, int MINWG, int MODE = 0>
+template <int NOB, int TR, int TS, int CG, int MINWG, int MODE = 0, bool NT = false>
 static hipError_t launch_one(const IgemmArgs& a, hipStream_t s) {
     if constexpr (MODE != 2) {   // partial strips: the masked-store instantiation
         if (a.Vo % 64 != 0) {
-            auto k = igemm_wreg_kernel<NOB, TR, TS, CG, MINWG, MODE, true>;
+            auto k = igemm_wreg_kernel<NOB, TR, TS, CG, MINWG, MODE, true, NT>;
             if (a.lds_bytes > 64 * 1024) {
                 hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);
@@ -625,7 +630,7 @@ static hipError_t launch_one(const IgemmArgs& a, hipStream_t s) {
             return hipGetLastError();
         }
     }
-    auto k = igemm_wreg_kernel<NOB, TR, TS, CG, MINWG, MODE>;
+    auto k = igemm_wreg_kernel<NOB, TR, TS, CG, MINWG, MODE, false, NT>;
     if (a.lds_bytes > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, a.lds_bytes);
@@ -645,7 +650,8 @@ hipError_t launch_igemm_wreg(const IgemmArgs& a, hipStream_t s) {
     }
     if (a.phase) {
 #define DC_WREG_PH(nob, t) \
-        if (NOB == nob && a.Tr == t && a.Ts == t) return launch_one<nob, t, t, 1, 1, 1>(a, s);
+        if (NOB == nob && a.Tr == t && a.Ts == t) \
+            return a.nt ? launch_one<nob, t, t, 1, 1, 1, true>(a, s) : launch_one<nob, t, t, 1, 1, 1>(a, s);
         DC_WREG_PH(2, 4) DC_WREG_PH(1, 4) DC_WREG_PH(2, 2) DC_WREG_PH(1, 2) DC_WREG_PH(2, 3) DC_WREG_PH(1, 3)
 #undef DC_WREG_PH
         return hipErrorInvalidValue;

@@ -100,7 +100,7 @@ struct IgemmArgs {
     int own;                     // interior launch: width of the margins, which no stored output reads
     int tsep;                    // fp32: the small part products have sums of their own
     int tkg, tgrec;              // groups of waves that share the channel chunks (1 or 2), their LDS records
-    int nt;                      // outputs leave by non-temporal stores (blocked, rolling-row kernels)
+    int nt;                      // outputs leave by non-temporal stores (blocked, rolling-row, phase-image kernels)
     uint32_t tmt, tmpg, tmbv, tmnf;   // 2^32 / d + 1 of the kernel's divisors (0 for 1)
     int nvb, nseg, rows_per_seg; // strip kernels: 64- (128-, rolling) column strips, row segments
     // frame mode (chunked and frame kernels): the launch covers only the
