@@ -44,7 +44,15 @@ int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t shmem, hi
 }
 
 int hipGetDevice(int* d) { *d = 0; return 0; }
-int hipDeviceGetAttribute(int* v, int attr, int dev) { (void)attr; (void)dev; *v = 160 * 1024; return 0; }
+/* compute units and LDS of a workgroup; the attribute numbers come from the HIP header */
+int hipDeviceGetAttribute(int* v, int attr, int dev)
+{
+    (void)dev;
+    if (attr == STUB_ATTR_CUS) *v = 256;
+    else if (attr == STUB_ATTR_LDS) *v = 160 * 1024;
+    else { fprintf(stderr, "unknown device attribute %d\n", attr); abort(); }
+    return 0;
+}
 int hipFuncSetAttribute(const void* f, int attr, int v) { (void)f; (void)attr; (void)v; return 0; }
 int hipGetLastError(void) { return 0; }
 int hipGetSymbolAddress(void** p, const void* sym) { *p = (void*)sym; return 0; }

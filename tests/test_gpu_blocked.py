@@ -240,3 +240,67 @@ def test_fp32_few_channels_keep_their_accuracy(C, K, R):
     steps = groups // 2 * R * R + groups % 2 * ((R * R + 1) // 2)
     err = _rel(y, orc.conv_fwd(x, w, L.stride, L.pad))
     assert err <= 2.0 ** -24 / 3 ** 0.5 * (steps / 2 + 1) ** 0.5, err
+
+
+# One layer or more for every block shape, staging and wave grouping that the planner
+# picks over the sizes programs run (4,000 layers drawn from classification, tile and
+# mesh models) and that the layers above do not reach.
+SHAPES = [
+    _layer("f32", 16, 48, 8, 38, 131, 1), _layer("f32", 1, 8, 8, 44, 8, 1, 2), _layer("f32", 2, 8, 8, 4, 6, 1, 2),
+    _layer("f32", 16, 40, 96, 141, 27, 1, 2), _layer("f32", 16, 32, 8, 25, 145, 3), _layer("f32", 2, 128, 8, 108, 146, 3),
+    _layer("f32", 16, 64, 40, 12, 84, 3), _layer("f32", 4, 8, 136, 94, 66, 3, 2), _layer("f32", 1, 24, 16, 83, 5, 3, 2),
+    _layer("f32", 1, 8, 40, 64, 8, 3, 2), _layer("f32", 2, 24, 16, 28, 19, 3, 2), _layer("f32", 2, 72, 64, 31, 67, 3, 2),
+    _layer("f32", 4, 24, 136, 59, 115, 3, 2), _layer("f32", 4, 192, 96, 70, 71, 3, 2),
+    _layer("bf16", 1, 8, 8, 5, 5, 1), _layer("bf16", 4, 8, 32, 139, 69, 1), _layer("bf16", 1, 8, 24, 4, 6, 1),
+    _layer("bf16", 16, 72, 8, 19, 109, 1), _layer("bf16", 16, 8, 264, 55, 17, 1), _layer("bf16", 16, 40, 8, 62, 100, 1),
+    _layer("bf16", 16, 96, 24, 18, 108, 1), _layer("bf16", 16, 320, 24, 6, 165, 1), _layer("bf16", 8, 8, 72, 75, 177, 1, 2),
+    _layer("bf16", 16, 512, 24, 5, 147, 1, 2), _layer("bf16", 1, 40, 8, 67, 4, 1, 2), _layer("bf16", 1, 96, 96, 4, 7, 1, 2),
+    _layer("bf16", 8, 128, 8, 17, 112, 3), _layer("bf16", 16, 8, 128, 9, 175, 3), _layer("bf16", 16, 136, 48, 105, 7, 3),
+    _layer("bf16", 8, 48, 24, 72, 127, 3), _layer("bf16", 16, 96, 136, 50, 10, 3), _layer("bf16", 1, 16, 136, 6, 4, 3, 2),
+    _layer("bf16", 16, 128, 8, 28, 142, 3, 2), _layer("bf16", 8, 40, 24, 87, 176, 3, 2), _layer("bf16", 1, 32, 64, 128, 4, 3, 2),
+    _layer("bf16", 4, 8, 136, 85, 144, 3, 2), _layer("bf16", 8, 8, 128, 65, 179, 3, 2), _layer("bf16", 1, 8, 48, 4, 6, 5, 2),
+    _layer("bf16", 1, 40, 48, 5, 4, 5, 2), _layer("bf16", 1, 16, 16, 8, 4, 7, 2), _layer("bf16", 16, 8, 320, 58, 22, 7, 2),
+    # weights gathered: channel counts that are no multiples of 8
+    _layer("bf16", 2, 77, 9, 4, 6, 1, 2), _layer("bf16", 16, 33, 25, 56, 139, 1, 2), _layer("bf16", 1, 13, 130, 4, 5, 1, 2),
+    _layer("bf16", 1, 9, 25, 36, 13, 1, 2), _layer("bf16", 1, 9, 33, 6, 4, 3, 2), _layer("bf16", 2, 33, 13, 4, 5, 3, 2),
+    _layer("bf16", 16, 33, 13, 49, 153, 3, 2), _layer("bf16", 16, 33, 33, 111, 81, 3, 2),
+]
+
+
+@pytest.mark.parametrize("L", SHAPES, ids=_id)
+def test_every_planned_block_shape_matches_oracle(L):
+    """Forward adds up to 4608 products, a weight gradient up to 330,000, in 32 bits: with
+    random signs sqrt(n) * 2^-25 of the largest sums, at most 1.7e-5 of the rms sum and, over
+    a maximum of four times that, 4.3e-6 of it; 1e-5."""
+    print(f"[shapes] {_id(L)}", flush=True)
+    x, w, dy = (wl.draw(L, t) for t in ("x", "w", "dy"))
+    for name, got, ref in zip(("y", "dx", "dw"), _run(L, x, w, dy), _oracle(L, x, w, dy)):
+        err = float(np.max(np.abs(got.astype(np.float64) - ref)) / np.max(np.abs(ref)))
+        assert np.all(np.isfinite(got)) and err <= 1e-5, (name, err)
+
+
+@pytest.mark.parametrize("dtype,C,K,Hh,W,R,S,stride,pad,halo", [
+    # partials of whole channel blocks past the allocation-free array, of the row kernels not
+    ("bf16", 33, 290000, 4, 3, 1, 1, 2, 0, 0), ("bf16", 33, 69000, 8, 4, 2, 2, 2, 0, 0), ("bf16", 33, 31000, 6, 4, 3, 3, 2, 1, 1),
+    ("bf16", 33, 16500, 8, 6, 4, 4, 2, 1, 2), ("bf16", 33, 12000, 9, 6, 5, 5, 2, 2, 2), ("bf16", 33, 7600, 8, 8, 6, 6, 2, 2, 3),
+    ("bf16", 33, 6000, 10, 8, 7, 7, 2, 3, 3), ("f32", 205, 15368, 6, 5, 4, 1, 1, 2, 3)])
+def test_row_kernels_of_very_wide_layers(dtype, C, K, Hh, W, R, S, stride, pad, halo):
+    """The row kernels behind dc_conv_bwd_filter_noalloc on layers whose dw nearly fills its
+    array: sampled entries against 64 bits (up to 80 products each, 1e-5 of the largest)."""
+    L = Layer("rows", 2, C, K, Hh, W, R, S, stride, pad, 1, 1, halo, dtype, "uniform", 990 + R)
+    print(f"[rows] {_id(L)}", flush=True)
+    p = dc.Problem.of(L)
+    x, dy = wl.draw(L, "x"), wl.draw(L, "dy")
+    xt, dyt = H.alloc_tiles(p, X, 1, dtype, fill=0.0), H.alloc_tiles(p, DY, 1, dtype)
+    H.scatter_interiors(xt, H.to_device(x, dtype), p, X)
+    H.scatter_interiors(dyt, H.to_device(dy, dtype), p, DY)
+    dw = torch.full((K, C, R, S), float("nan"), device="cuda")
+    assert dc.bwd_filter_workspace_bytes(p, 0) <= dc.BWD_FILTER_NOALLOC_MAX_BYTES
+    dc.conv_bwd_filter_noalloc(p, 0, xt, dyt, dw, 0)
+    torch.cuda.synchronize()
+    rng = np.random.default_rng(3)
+    o = np.unique(np.concatenate([rng.integers(0, K, 60), [0, 63, 64, K - 1]]))
+    sub = dy[:, o]
+    ref = orc.conv_bwd_filter(x, np.ascontiguousarray(sub), R, S, stride, pad)
+    got = dw[torch.from_numpy(o).cuda()].cpu().numpy()
+    assert bool(torch.isfinite(dw).all()) and np.max(np.abs(got - ref)) <= 1e-5 * np.max(np.abs(ref))

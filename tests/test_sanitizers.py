@@ -56,8 +56,14 @@ def test_library_host_code_under_asan_and_ubsan(tmp_path):
     fat = sorted(set(re.findall(r"\b(__hip_fatbin_[0-9a-f]+)\b", undef)))
     stub_fat = tmp_path / "fatbins.c"
     stub_fat.write_text("".join(f"char {s}[16];\n" for s in fat))
+    attrs = tmp_path / "attrs.cpp"
+    attrs.write_text("#include <hip/hip_runtime_api.h>\n#include <cstdio>\nint main() { printf(\"%d %d\", "
+                     "int(hipDeviceAttributeMultiprocessorCount), int(hipDeviceAttributeMaxSharedMemoryPerBlock)); }\n")
+    _run([HIPCC, "-x", "hip", "--offload-host-only", "-w", str(attrs), "-o", str(tmp_path / "attrs")])
+    cus, lds = _run([str(tmp_path / "attrs")]).stdout.split()
     exe = str(tmp_path / "host_checks")
-    _run([CLANG, "-O1", "-g", *SAN_FLAGS, "-I", os.path.join(ROOT, "include"), "-o", exe,
+    _run([CLANG, "-O1", "-g", *SAN_FLAGS, f"-DSTUB_ATTR_CUS={cus}", f"-DSTUB_ATTR_LDS={lds}",
+          "-I", os.path.join(ROOT, "include"), "-o", exe,
           os.path.join(SAN, "host_checks.c"), os.path.join(SAN, "hip_stub.c"), str(stub_fat), *objs,
           "-lstdc++", "-lm", "-lpthread"])
     r = _run([exe], env=ENV)
