@@ -128,6 +128,14 @@ typedef struct {
 /* ---- the five operations ---- */
 
 /*
+ * Arithmetic.  Products of bf16 inputs are exact, those of fp32 inputs exact or,
+ * in layers that run on the bf16 matrix instruction with each value split in
+ * three bf16 parts, within 2^-24 of a product; sums are fp32 in a fixed order.
+ * Infinities, NaN and values at the ends of fp32's range are taken whole: outputs
+ * that read them are formed with the fp32 instruction, no others are.
+ */
+
+/*
  * Forward propagation on one tile, Eq. (1) (Sec. II-A) restricted to the
  * tile's samples and output pixels (Sec. III-A):
  *   y[n,k,p,q] = sum_{c,r,s} x[n,c, p*stride-pad+r, q*stride-pad+s] * w[k,c,r,s]

@@ -22,23 +22,27 @@
 // transposed on the way in: 16-byte loads of 8 channels, one byte permute per
 // two values.
 //
-// fp32 layers run on the same matrix instruction.  Each value is split into
-// three bf16 parts that add up to it exactly (three roundings to nearest, 24
-// bits), and the product is formed from the six part products of weight above
-// 2^-24 (parts 0*0, 0*1, 1*0, 1*1, 0*2, 2*0); what is left out is about 2^-26
-// of a product and of random sign.  Six bf16 MFMAs take 16 channels in 192
-// cycles; v_mfma_f32_32x32x2_f32 takes 512.  A block that meets values the
-// parts cannot hold (infinities, NaN, magnitudes near the ends of the range)
-// is computed once more on the fp32 instruction, from the same staging, for
-// the outputs that read them.
+// fp32 layers run on the same matrix instruction.  A value from 2^-110 on is
+// split into three bf16 parts that add up to it exactly (three roundings to
+// nearest, 24 bits), and the product is formed from six part products (parts
+// 0*0, 0*1, 1*0, 1*1, 0*2, 2*0); the three left out come to at most 2^-24 of a
+// product, 2^-26 as a rule, of random sign.  Where it took over in 160 fp32 layers
+// of mesh models, the error against 64 bits is 0.64 (forward) and 0.69 (input
+// gradient) of the fp32 instruction's (geometric means; no layer above it): 16
+// channels are added in eight steps there, in six here.  With the products of
+// parts 1*2 and 2*1 as well no layer's error changed by 1 %, at 2 to 5 % more
+// time.  Six bf16 MFMAs take 16 channels in 192 cycles; v_mfma_f32_32x32x2_f32
+// takes 512.  A block that meets values the parts cannot hold (infinities, NaN,
+// magnitudes near the ends of the range) is computed once more on the fp32
+// instruction, from the same staging, for the outputs that read them.
 //
 // Bound: the matrix cores at many channels; what holds it is staging (waits
 // for loads and barriers, 2 waves per SIMD).  Measured against the chunked
 // kernel it replaces for these layers (us a pass): 128 -> 128 channels 3x3 on
 // 32 images of 28x28, bf16: 131 -> 21; 256 -> 256 3x3 stride 2 on 28x28:
 // forward 286 -> 35, backward-data 274 -> 33; fp32 128 -> 128 3x3 on a 64x64
-// tile: 208 -> 43 and 210 -> 40; fp32 32 -> 32 stride 2 on a 512x512 tile,
-// backward-data: 89 -> 20.
+// tile: 208 -> 28 and 210 -> 24; fp32 32 -> 32 stride 2 on a 512x512 tile,
+// backward-data: 89 -> 17.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -169,17 +173,17 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
             const int rest = div16(e, a.tmt), t = e - rest * T;
             const int o = a.wmode ? rest % OB : rest / CCG;
             cg = a.wmode ? rest / OB : rest % CCG;
-            off = in_lds & (o0 + o < a.Cout) ? uint32_t(int((o0 + o) * a.w_os) + t) * ES + cg * 8 * wstep : kTileOut;
+            off = (in_lds & (o0 + o < a.Cout)) ? uint32_t(int((o0 + o) * a.w_os) + t) * ES + cg * 8 * wstep : kTileOut;
             slot = in_lds ? t * TREC + cg * GREC + o : -1;
         } else if constexpr (WM == kWRows) {
             cg = e % CCG;
             const int o = e / CCG;
-            off = in_lds & (o0 + o < a.Cout) ? uint32_t((o0 + o) * int(a.w_os)) * ES + cg * 8 * wstep : kTileOut;
+            off = (in_lds & (o0 + o < a.Cout)) ? uint32_t((o0 + o) * int(a.w_os)) * ES + cg * 8 * wstep : kTileOut;
             slot = in_lds ? cg * GREC + o : -1;
         } else {
             cg = div16(e, a.tmnf);
             const int f = (e - cg * NFG) * 8;
-            off = in_lds & (o0 * T + f < a.Cout * T) ? uint32_t(o0 * T + f) * ES + cg * 8 * wstep : kTileOut;
+            off = (in_lds & (o0 * T + f < a.Cout * T)) ? uint32_t(o0 * T + f) * ES + cg * 8 * wstep : kTileOut;
             slot = in_lds ? f : -1;
         }
     };
@@ -621,44 +625,44 @@ __device__ __forceinline__ bool igemm_tile_sweep(const IgemmArgs& a, unsigned ch
     float* out = a.out + tile * a.out_tile + int64_t(n) * a.Cout * oplane;
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, a.Cout * oplane * 4, kTileWord3);
     auto finish = [&](auto ntc) __attribute__((always_inline)) {
-    constexpr int AUX = decltype(ntc)::value;
+        constexpr int AUX = decltype(ntc)::value;
 #pragma unroll
-    for (int j = 0; j < NPBW; ++j) {
-        const int p = (wp * NPBW + j) * 32 + l32;
-        const int ul = div16(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
-        const bool live = (p < np) & (v < a.Vo);
+        for (int j = 0; j < NPBW; ++j) {
+            const int p = (wp * NPBW + j) * 32 + l32;
+            const int ul = div16(p, a.tmbv), u = u0 + ul, v = v0 + p - ul * bv;
+            const bool live = (p < np) & (v < a.Vo);
 #pragma unroll
-        for (int i = 0; i < NOBW; ++i) {
-            const int ob0 = o0 + (wo * NOBW + i) * 32 + 4 * hi;
-            if constexpr (BP) {
+            for (int i = 0; i < NOBW; ++i) {
+                const int ob0 = o0 + (wo * NOBW + i) * 32 + 4 * hi;
+                if constexpr (BP) {
 #pragma unroll
-                for (int py = 0; py < 2; ++py) {
-                    const int orow = 2 * u + py, ocol = 2 * v;
-                    const bool ok = live && orow < a.out_rows, both = ocol + 1 < a.out_cols;
+                    for (int py = 0; py < 2; ++py) {
+                        const int orow = 2 * u + py, ocol = 2 * v;
+                        const bool ok = live && orow < a.out_rows, both = ocol + 1 < a.out_cols;
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int o = ob0 + 8 * (e / 4) + e % 4;
+                            const uint32_t off = (o * oplane + orow * a.out_cols + ocol) * 4;
+                            const float f0 = acc[2 * py][i][j][e], f1 = acc[2 * py + 1][i][j][e];
+                            typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+                            const u32x2 w2 = {__builtin_bit_cast(u32, f0), __builtin_bit_cast(u32, f1)};
+                            __builtin_amdgcn_raw_buffer_store_b64(w2, rout, (ok & both & (o < a.Cout)) ? off : kTileOut, 0, AUX);
+                            if (!both & ok & (o < a.Cout)) __builtin_amdgcn_raw_buffer_store_b32(w2[0], rout, off, 0, AUX);
+                        }
+                    }
+                } else {
+                    const int orow = u * a.ostr + a.oph_r, ocol = v * a.ostr + a.oph_c;
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
                         const int o = ob0 + 8 * (e / 4) + e % 4;
                         const uint32_t off = (o * oplane + orow * a.out_cols + ocol) * 4;
-                        const float f0 = acc[2 * py][i][j][e], f1 = acc[2 * py + 1][i][j][e];
-                        typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-                        const u32x2 w2 = {__builtin_bit_cast(u32, f0), __builtin_bit_cast(u32, f1)};
-                        __builtin_amdgcn_raw_buffer_store_b64(w2, rout, ok & both & (o < a.Cout) ? off : kTileOut, 0, AUX);
-                        if (!both & ok & (o < a.Cout)) __builtin_amdgcn_raw_buffer_store_b32(w2[0], rout, off, 0, AUX);
+                        const float f = acc[0][i][j][e];
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, f), rout,
+                                                              (live & (o < a.Cout)) ? off : kTileOut, 0, AUX);
                     }
-                }
-            } else {
-                const int orow = u * a.ostr + a.oph_r, ocol = v * a.ostr + a.oph_c;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int o = ob0 + 8 * (e / 4) + e % 4;
-                    const uint32_t off = (o * oplane + orow * a.out_cols + ocol) * 4;
-                    const float f = acc[0][i][j][e];
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, f), rout,
-                                                          live & (o < a.Cout) ? off : kTileOut, 0, AUX);
                 }
             }
         }
-    }
     };
     if constexpr (!RAW) {
         bool again = false;

@@ -84,8 +84,8 @@ bool wgrad_tile_plan(int dtype, int ntiles, int N, int C, int K, int R, int S, i
     // Chunks: at most one workgroup per CU, and 64 MiB of partials (what the
     // allocation-free entry point holds) where one chunk's stay below it; more of them shorten the walk over the
     // pixel blocks (matrix work and about 1 us of barriers and exposed latency
-    // each), fewer move less: each chunk writes and reads F floats at about
-    // 10 TB/s.  Above eight a whole number per XCD, so that the blocks of one chunk
+    // each), fewer move less: each chunk writes and reads F floats, taken
+    // at 10 TB/s (most of them stay in the caches).  Above eight a whole number per XCD, so that the blocks of one chunk
     // share an L2.
     const int64_t most = std::max<int64_t>(1, std::min<int64_t>({std::max(1, device_cu_count() / (t->gy * t->gz)),
                                                                   (int64_t(64) << 20) / (t->F * 4), t->tnpb}));
